@@ -156,8 +156,9 @@ enum set_pipeline {
     /* A batch of vector jobs in one launch graph: H2D of a descriptor table
      * (64-byte header + one 48-byte descriptor per job, each with its own
      * work-item size) -> a persistent
-     * kernel whose blocks pull (job, tile) work items from an atomic counter
-     * -> a kernel summing each job's tile partials in tile order -> D2H of
+     * kernel whose blocks pull (job, tile) work items, or equal parts of them,
+     * from an atomic counter -> a kernel summing each job's tile partials in
+     * a fixed order -> D2H of
      * set_out_header + one float32 S per job, in descriptor order.  Jobs are
      * normally submitted through set_run_vector_jobs, which builds the
      * tables; per-job S depends only on (n, tile size). */

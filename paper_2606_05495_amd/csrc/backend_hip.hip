@@ -844,7 +844,7 @@ class HipBackend : public Backend {
                           : vbb == 1024 ? (const void*)&k_vec_batch_tiles<1024>
                                         : (const void*)&k_vec_batch_tiles<256>;
         stage(vbk, dim3(t.grid > 0 ? (unsigned)t.grid : (unsigned)kVecBatchGrid), &sl.vb, (unsigned)vbb);
-        stage((const void*)&k_vec_batch_final, dim3((t.batch_max + kBlock - 1) / kBlock), &sl.vbf);
+        stage((const void*)&k_vec_batch_final, dim3((t.batch_max + kVecFinalJobs - 1) / kVecFinalJobs), &sl.vbf);
         break;
       }
       case SET_PIPE_HOTSPOT_F32: {

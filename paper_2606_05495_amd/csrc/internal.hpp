@@ -73,21 +73,39 @@ static_assert(sizeof(set_job_template) == 96, "set_job_template layout");
 // Descriptor table of a vector batch (host-written, copied to the slot by
 // the batch's H2D): a 64-byte header, then one 48-byte descriptor per job.
 // Each job carries its own work-item size, so one batch may mix size buckets
-// while every job's result still depends only on (n, its item size).
+// while every job's result still depends only on (n, its item size).  A tile is
+// what a block takes: a work item, or one of its units (vec_unit_elems).
 struct VecBatchHdr {
   uint32_t count;        // jobs in the batch
-  uint32_t total_tiles;  // work items in the batch
-  uint32_t pad[14];
+  uint32_t total_tiles;  // tiles in the batch
+  uint32_t claim;        // tiles a block claims at a time (vec_claim)
+  uint32_t pad[13];
 };
 struct VecBatchDesc {
   uint64_t x_off, y_off;
   uint32_t n;
   float a;
-  uint32_t tile_start;   // first work item of this job (non-decreasing)
+  uint32_t tile_start;   // first tile of this job (non-decreasing)
   uint32_t ntiles;       // ceil(n / tile_elems)
-  uint32_t tile_elems;   // elements per work item, multiple of 1024
-  uint32_t pad[3];
+  uint32_t tile_elems;   // elements per tile, multiple of 256
+  uint32_t unit_elems;   // elements per unit: tile_elems, or an equal part of it
+  uint32_t per_item;     // tiles per work item
+  uint32_t pad;
 };
+// Tile geometry of a job of n elements with work items of item_elems, for
+// blocks of `block` threads; split: tiles are units.
+SETRT_HD inline void vec_set_tiles(VecBatchDesc& d, uint32_t n, uint32_t item_elems, int block, bool split) {
+  d.n = n;
+  d.unit_elems = vec_unit_elems(item_elems, block);
+  d.tile_elems = split ? d.unit_elems : item_elems;
+  d.per_item = item_elems / d.tile_elems;
+  d.ntiles = (uint32_t)(((uint64_t)n + d.tile_elems - 1) / d.tile_elems);
+  d.pad = 0;
+}
+inline uint64_t vec_units(uint64_t n, uint32_t item_elems, int block) {
+  const uint32_t u = vec_unit_elems(item_elems, block);
+  return (n + u - 1) / u;
+}
 static_assert(sizeof(VecBatchHdr) == 64, "VecBatchHdr layout");
 static_assert(sizeof(VecBatchDesc) == 48, "VecBatchDesc layout");
 

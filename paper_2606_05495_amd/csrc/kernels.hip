@@ -416,24 +416,6 @@ __device__ inline float from_right(float v, float edge) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
 }
 
-// Sum over the wave in six DPP steps: two quad permutes, the half-row and row
-// mirrors (each lane then holds its 16-lane row's sum), then row_bcast:15 into
-// rows 1 and 3 and row_bcast:31 into rows 2 and 3; lane 63 ends with the total,
-// which readlane returns to every lane.  Lanes of rows a broadcast leaves out
-// add the old value 0.  The order of the additions is fixed.
-template <int CTRL, int ROWS = 0xf>
-__device__ inline int dpp_i(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
-}
-__device__ inline float wave_total_f32(float v) {
-  v += __int_as_float(dpp_i<0xb1>(__float_as_int(v)));        // quad_perm [1,0,3,2]
-  v += __int_as_float(dpp_i<0x4e>(__float_as_int(v)));        // quad_perm [2,3,0,1]
-  v += __int_as_float(dpp_i<0x141>(__float_as_int(v)));       // row_half_mirror
-  v += __int_as_float(dpp_i<0x140>(__float_as_int(v)));       // row_mirror
-  v += __int_as_float(dpp_i<0x142, 0xa>(__float_as_int(v)));  // row_bcast:15
-  v += __int_as_float(dpp_i<0x143, 0xc>(__float_as_int(v)));  // row_bcast:31
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
 __device__ inline uint32_t wave_total_u32(uint32_t v) {
   int x = (int)v;
   x += dpp_i<0xb1>(x);
@@ -949,38 +931,110 @@ __global__ __launch_bounds__(kBlock) void k_sobel_final(SobelFinalArgs a) {
 }
 
 // ------------------------------------------------------------------ vector job: S = sum tanh(a*x + y)
-// Block b reduces elements [b*C, min((b+1)*C, n)), C = vec_chunk(n, grid),
-// with 16-byte loads when both windows are 4-element aligned.
+// tanh in 30 instruction slots (a transcendental counts as four) where the
+// library function takes about 45: two divergent branches, and most waves run
+// both, which bounded every vector kernel on long jobs.  Here both forms are
+// evaluated and one is selected:
+//  |z| < 0.8: odd polynomial z + z*s*P(s), s = z^2.  P is the degree-5 minimax
+//    fit of (tanh(z)/z - 1)/s, weighted to the relative error of the whole
+//    (Lawson iteration over 4000 Chebyshev points; largest error 3.7e-9).
+//  otherwise 1 - 2/(e + 1) with e = exp(2|z|) = 2^(2 log2(e) |z|) from the
+//    hardware exponential and reciprocal (1 ulp each); the rounding error of
+//    the exponent and of its constant, lo, goes back in as e += e ln2 lo.
+//    |z| is capped at 10, where the result is 1 in float32 and e is finite.
+// A NaN fails the comparison and leaves through the polynomial.
+__device__ inline float tanh_f32(float z) {
+  const float s = z * z;
+  float p = fmaf(s, 0.00158475642f, -0.0074095577f);
+  p = fmaf(s, p, 0.0213029906f);
+  p = fmaf(s, p, -0.0538523309f);
+  p = fmaf(s, p, 0.133322209f);
+  p = fmaf(s, p, -0.333332986f);
+  const float small = fmaf(z * s, p, z);
+  const float w = fminf(fabsf(z), 10.f);
+  const float x = w * 2.88539004f;  // 2 log2(e), rounded
+  const float lo = fmaf(w, 3.851926e-08f, fmaf(w, 2.88539004f, -x));
+  float e = __builtin_amdgcn_exp2f(x);
+  e = fmaf(e * 0.693147182f, lo, e);
+  const float big = copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(e + 1.f), 1.f), z);
+  return fabsf(z) >= 0.8f ? big : small;
+}
+
+// Four floats at any float's address: gfx950 loads 16 bytes from 4-byte
+// aligned addresses, so windows at every offset take the same path.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// Thread's share of sum tanh(a*x + y) over len elements, by a block of BLOCK
+// threads: thread j takes the 4-element groups j, j + BLOCK, ... in order, and
+// thread 0 the last len % 4 elements.  The order depends on len and BLOCK only.
+// U groups (2 U 16-byte loads a thread) are in flight at once; with one, a block
+// moved 32 bytes a thread per memory round trip, and calls of a few long jobs
+// were bound by latency.  U = 4 keeps the kernel within 64 registers, so that
+// eight waves fit a SIMD.
+// x, y and len are the same in every thread.
+template <int BLOCK>
+__device__ __forceinline__ float vec_range_sum(const float* x, const float* y, float av, uint64_t len) {
+  constexpr int U = 4;
+  constexpr uint64_t kRow = 16ull * BLOCK;  // bytes of one row of groups
+  const uint64_t ng = len >> 2;
+  const uint32_t off = 16u * threadIdx.x;
+  uint64_t px = reinterpret_cast<uint64_t>(x), py = reinterpret_cast<uint64_t>(y);
+  auto load = [&](uint64_t base) {
+    uint32_t o = off;
+    asm("" : "+s"(base), "+v"(o));  // scalar row base + 32-bit lane offset
+    return *reinterpret_cast<const v4f_any __attribute__((address_space(1)))*>(base + o);
+  };
+  float acc = 0.f;
+  auto quad = [&](v4f_any xv, v4f_any yv) {
+    return (tanh_f32(fmaf(av, xv.x, yv.x)) + tanh_f32(fmaf(av, xv.y, yv.y))) +
+           (tanh_f32(fmaf(av, xv.z, yv.z)) + tanh_f32(fmaf(av, xv.w, yv.w)));
+  };
+  uint64_t g = 0;
+  for (; g + U * BLOCK <= ng; g += U * BLOCK) {
+    v4f_any xv[U], yv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xv[u] = load(px + kRow * u);
+      yv[u] = load(py + kRow * u);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // every load goes out before the first result is formed
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += quad(xv[u], yv[u]);
+    px += kRow * U;
+    py += kRow * U;
+  }
+  // Less than U rows of groups are left, the last perhaps part of a row: all
+  // loads first (a thread past the end loads nothing), then the sums.
+  const uint32_t left = (uint32_t)(ng - g);
+  v4f_any xv[U], yv[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u * BLOCK + threadIdx.x < left) {
+      xv[u] = load(px + kRow * u);
+      yv[u] = load(py + kRow * u);
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u * BLOCK + threadIdx.x < left) acc += quad(xv[u], yv[u]);
+  if ((len & 3u) && threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < (int)(len & 3u)) acc += tanh_f32(fmaf(av, x[4 * ng + k], y[4 * ng + k]));
+  }
+  return acc;
+}
+
+// Block b reduces elements [b*C, min((b+1)*C, n)), C = vec_chunk(n, grid).
 __global__ __launch_bounds__(kBlock) void k_saxpy_tanh_sum_f32(VecArgs a) {
   __shared__ float s4f[4];
   const JobScalars js = a.js;
   if (blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, js);
   const uint64_t n = js.n;
-  const unsigned G = gridDim.x;
-  const uint64_t C = vec_chunk(n, G);
+  const uint64_t C = vec_chunk(n, gridDim.x);
   const uint64_t beg = (uint64_t)blockIdx.x * C;
   const uint64_t end = beg + C < n ? beg + C : n;
-  const float* __restrict__ x = a.x + js.x_off;
-  const float* __restrict__ y = a.y + js.y_off;
-  const float av = js.a;
   float acc = 0.f;
-  if (beg < end) {
-    if (((js.x_off | js.y_off) & 3u) == 0) {
-      const uint64_t vend = beg + ((end - beg) & ~3ull);
-      for (uint64_t i = beg + 4ull * threadIdx.x; i < vend; i += 4ull * kBlock) {
-        const float4 xv = *reinterpret_cast<const float4*>(x + i);
-        const float4 yv = *reinterpret_cast<const float4*>(y + i);
-        acc += tanhf(fmaf(av, xv.x, yv.x));
-        acc += tanhf(fmaf(av, xv.y, yv.y));
-        acc += tanhf(fmaf(av, xv.z, yv.z));
-        acc += tanhf(fmaf(av, xv.w, yv.w));
-      }
-      if (threadIdx.x == 0)
-        for (uint64_t i = vend; i < end; ++i) acc += tanhf(fmaf(av, x[i], y[i]));
-    } else {
-      for (uint64_t i = beg + threadIdx.x; i < end; i += kBlock) acc += tanhf(fmaf(av, x[i], y[i]));
-    }
-  }
+  if (beg < end) acc = vec_range_sum<kBlock>(a.x + js.x_off + beg, a.y + js.y_off + beg, js.a, end - beg);
   const float bs = block_sum_f32(acc, s4f);
   if (threadIdx.x == 0) a.partials[blockIdx.x] = bs;
 }
@@ -1010,32 +1064,6 @@ __global__ __launch_bounds__(kBlock) void k_vec_final(VecFinalArgs a) {
 }
 
 // ------------------------------------------------------------------ vector batch: persistent (job, tile) kernel
-// Every block loops: take the next work item from the batch's counter, find
-// its job by binary search over the descriptors' first-item indices, reduce
-// that item's elements (fixed order within the item) and store the item's
-// partial.  Which block takes which item does not change any result.
-template <int BLOCK>
-__device__ inline float vec_range_sum(const float* __restrict__ x, const float* __restrict__ y, float av,
-                                      uint64_t beg, uint64_t end, bool aligned) {
-  float acc = 0.f;
-  if (aligned) {
-    const uint64_t vend = beg + ((end - beg) & ~3ull);
-    for (uint64_t i = beg + 4ull * threadIdx.x; i < vend; i += 4ull * BLOCK) {
-      const float4 xv = *reinterpret_cast<const float4*>(x + i);
-      const float4 yv = *reinterpret_cast<const float4*>(y + i);
-      acc += tanhf(fmaf(av, xv.x, yv.x));
-      acc += tanhf(fmaf(av, xv.y, yv.y));
-      acc += tanhf(fmaf(av, xv.z, yv.z));
-      acc += tanhf(fmaf(av, xv.w, yv.w));
-    }
-    if (threadIdx.x == 0)
-      for (uint64_t i = vend; i < end; ++i) acc += tanhf(fmaf(av, x[i], y[i]));
-  } else {
-    for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK) acc += tanhf(fmaf(av, x[i], y[i]));
-  }
-  return acc;
-}
-
 // Pairwise sum of W values in a fixed tree ((s0+s1)+(s2+s3)) + ...
 template <int W>
 __device__ inline float tree_sum_f32(const float* s) {
@@ -1046,51 +1074,96 @@ __device__ inline float tree_sum_f32(const float* s) {
   }
 }
 
-// Block sum of a BLOCK-thread block: wave sums, then a fixed pairwise tree
-// over the waves (for 256 threads the same order as block_sum_f32).
-template <int BLOCK>
-__device__ inline float block_sum_f32_w(float v, float* sw) {
-  v = wave_sum_f32(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sw[wave] = v;
-  __syncthreads();
-  return tree_sum_f32<BLOCK / 64>(sw);
+// The job that owns tile t: the last descriptor whose first tile is <= t.  One
+// wave; every round its 64 lanes test 64 evenly spaced descriptors, so a table
+// of 4096 jobs takes two memory round trips where a binary search took twelve.
+__device__ inline uint32_t vec_find_job(const VecBatchDesc* D, uint32_t count, uint32_t t) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t lo = 0, n = count;  // the job is in [lo, lo + n), and D[lo] starts at or before t
+  while (n > 1) {
+    const uint32_t step = (n + 63) / 64;
+    const uint32_t at = lane * step;
+    const bool le = at < n && D[lo + at].tile_start <= t;
+    const uint32_t k = (uint32_t)__builtin_popcountll(__ballot(le)) - 1;  // lane 0 always tests true
+    lo += k * step;
+    n = n - k * step < step ? n - k * step : step;
+  }
+  return lo;
 }
 
+// A batch's tiles are claimed in runs of H->claim.  Block b starts with run b;
+// further runs come from the batch's counter, asked for before the loads of a
+// run's last tile and answered behind them.  Wave 0 finds the next tile's job
+// and leaves its descriptor in LDS; one barrier ends a tile (the LDS words are
+// double, so the next tile's writes cannot meet this one's reads).  A tile's
+// partial depends on its job and BLOCK only, so which block takes it changes no
+// result.
+// Bound by memory from about 100 MB a call: 7.1 TB/s over jobs of 2^20 and more
+// at every block size (256 threads: 6.7 before, with one pair of loads in
+// flight and the atomic and a binary search ahead of each unit); 64 uneven jobs,
+// 310 MB, 256 threads, on the no-allocation call: 181 us before, 70 us now.
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_vec_batch_tiles(VecBatchArgs a) {
-  __shared__ float s4f[BLOCK / 64];
-  __shared__ uint32_t s_item;
-  __shared__ uint32_t s_job;
+__global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
+  constexpr int W = BLOCK / 64;
+  __shared__ float s_sum[2][kVecUnitsPerItem][W];
+  __shared__ uint32_t s_tile[2];
+  __shared__ VecBatchDesc s_desc[2];
   if (blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
   const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
   const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
-  const uint32_t count = H->count, T = H->total_tiles;
+  const uint32_t count = H->count, T = H->total_tiles, run = H->claim;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  constexpr int kDescWords = sizeof(VecBatchDesc) / 4;
+  auto publish = [&](uint32_t t, int slot) {  // wave 0: tile t and its job's descriptor
+    if (t < T) {
+      const uint32_t j = vec_find_job(D, count, t);
+      if (lane < kDescWords)
+        reinterpret_cast<uint32_t*>(&s_desc[slot])[lane] = reinterpret_cast<const uint32_t*>(D + j)[lane];
+    }
+    if (lane == 0) s_tile[slot] = t;
+  };
+  const uint64_t first = (uint64_t)blockIdx.x * run, dealt = (uint64_t)gridDim.x * run;
+  if (first >= T) return;
+  int cur = 0;
+  uint32_t left = run;  // tiles of the run still to do, the current one included
+  if (wave == 0) publish((uint32_t)first, 0);
+  __syncthreads();
   while (true) {
-    if (threadIdx.x == 0) {
-      const uint32_t t = __hip_atomic_fetch_add(a.work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_item = t;
-      if (t < T) {
-        uint32_t lo = 0, hi = count - 1;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi + 1) >> 1;
-          if (D[mid].tile_start <= t) lo = mid; else hi = mid - 1;
-        }
-        s_job = lo;
+    const uint32_t t = __builtin_amdgcn_readfirstlane(s_tile[cur]);
+    if (t >= T) break;
+    uint32_t next = t + 1;
+    if (--left == 0) {
+      left = run;
+      next = T;
+      if (T > dealt && threadIdx.x == 0) {
+        const uint64_t u =
+            dealt + (uint64_t)run * __hip_atomic_fetch_add(a.work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        next = u < T ? (uint32_t)u : T;
       }
     }
+    const VecBatchDesc& d = s_desc[cur];
+    auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+    auto scalar64 = [&](uint64_t v) { return (uint64_t)scalar((uint32_t)(v >> 32)) << 32 | scalar((uint32_t)v); };
+    const uint32_t te = scalar(d.tile_elems), ue = scalar(d.unit_elems), n = scalar(d.n);
+    const uint64_t beg = (uint64_t)(t - scalar(d.tile_start)) * te;
+    const uint64_t len = beg + te < n ? te : n - beg;
+    const float av = __int_as_float((int)scalar((uint32_t)__float_as_int(d.a)));
+    const float* x = a.x + scalar64(d.x_off) + beg;
+    const float* y = a.y + scalar64(d.y_off) + beg;
+    int units = 0;
+    for (uint64_t u = 0; u < len; u += ue, ++units) {
+      const float ws = wave_total_f32(vec_range_sum<BLOCK>(x + u, y + u, av, len - u < ue ? len - u : ue));
+      if (lane == 0) s_sum[cur][units][wave] = ws;
+    }
+    if (wave == 0) publish(__builtin_amdgcn_readfirstlane(next), cur ^ 1);
     __syncthreads();
-    const uint32_t t = s_item;
-    if (t >= T) break;
-    const VecBatchDesc d = D[s_job];
-    const uint64_t beg = (uint64_t)(t - d.tile_start) * d.tile_elems;
-    const uint64_t end = beg + d.tile_elems < d.n ? beg + d.tile_elems : (uint64_t)d.n;
-    const float acc =
-        vec_range_sum<BLOCK>(a.x + d.x_off, a.y + d.y_off, d.a, beg, end, ((d.x_off | d.y_off) & 3u) == 0);
-    const float bs = block_sum_f32_w<BLOCK>(acc, s4f);
-    if (threadIdx.x == 0) a.partials[t] = bs;
-    __syncthreads();
+    if (threadIdx.x == 0) {
+      float s = tree_sum_f32<W>(s_sum[cur][0]);
+      for (int u = 1; u < units; ++u) s += tree_sum_f32<W>(s_sum[cur][u]);
+      a.partials[t] = s;
+    }
+    cur ^= 1;
   }
 }
 template __global__ void k_vec_batch_tiles<128>(VecBatchArgs);
@@ -1098,15 +1171,15 @@ template __global__ void k_vec_batch_tiles<256>(VecBatchArgs);
 template __global__ void k_vec_batch_tiles<512>(VecBatchArgs);
 template __global__ void k_vec_batch_tiles<1024>(VecBatchArgs);
 
-// Job j = thread: its items' partials added in item order.  Block 0 also
-// rewinds the work counter for the slot's next batch and publishes the header.
+// Job j = wave: its tiles' partials in a fixed order.  Block 0 also rewinds the
+// work counter for the slot's next batch and publishes the header.
 __global__ __launch_bounds__(kBlock) void k_vec_batch_final(VecBatchFinalArgs a) {
   const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
   const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
-  const uint32_t j = blockIdx.x * kBlock + threadIdx.x;
+  const uint32_t j = blockIdx.x * kVecFinalJobs + (threadIdx.x >> 6);
   if (j < H->count) {
-    const VecBatchDesc d = D[j];
-    a.results[j] = vec_items_total(a.partials, d.tile_start, d.ntiles);
+    const float s = vec_job_total(a.partials + D[j].tile_start, D[j].ntiles, D[j].per_item);
+    if ((threadIdx.x & 63) == 0) a.results[j] = s;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *a.work = 0u;

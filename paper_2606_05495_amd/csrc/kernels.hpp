@@ -85,7 +85,7 @@ struct VecBatchArgs {
   const float* x;
   const float* y;
   float* partials;     // [total_tiles]
-  uint32_t* work;      // work-item counter (zero between batches)
+  uint32_t* work;      // claim counter (zero between batches)
   DevSlotHdr* hdr;
   JobScalars js;
 };
@@ -221,13 +221,44 @@ __global__ void k_sobel_thresh_win_f32(SobelArgs a);
 __global__ void k_sobel_final(SobelFinalArgs a);
 __global__ void k_saxpy_tanh_sum_f32(VecArgs a);
 __global__ void k_vec_final(VecFinalArgs a);
-// Sum of one vector job's work-item partials in item order: the fixed order
-// that makes a job's result depend only on its length and item size.
-__device__ inline float vec_items_total(const float* partials, uint32_t first, uint32_t count) {
-  float s = 0.f;
-  for (uint32_t k = 0; k < count; ++k) s += partials[first + k];
-  return s;
+#if defined(__HIPCC__)
+// Sum over the wave in six DPP steps: two quad permutes, the half-row and row
+// mirrors (each lane then holds its 16-lane row's sum), then row_bcast:15 into
+// rows 1 and 3 and row_bcast:31 into rows 2 and 3; lane 63 ends with the total,
+// which readlane returns to every lane.  Lanes of rows a broadcast leaves out
+// add the old value 0.  The order of the additions is fixed.
+template <int CTRL, int ROWS = 0xf>
+__device__ inline int dpp_i(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
 }
+__device__ inline float wave_total_f32(float v) {
+  v += __int_as_float(dpp_i<0xb1>(__float_as_int(v)));        // quad_perm [1,0,3,2]
+  v += __int_as_float(dpp_i<0x4e>(__float_as_int(v)));        // quad_perm [2,3,0,1]
+  v += __int_as_float(dpp_i<0x141>(__float_as_int(v)));       // row_half_mirror
+  v += __int_as_float(dpp_i<0x140>(__float_as_int(v)));       // row_mirror
+  v += __int_as_float(dpp_i<0x142, 0xa>(__float_as_int(v)));  // row_bcast:15
+  v += __int_as_float(dpp_i<0x143, 0xc>(__float_as_int(v)));  // row_bcast:31
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+// Sum of one vector job's tile partials by one wave: a work item's tiles in
+// order, lane l the items l, l + 64, ..., then the lanes' sums.  Items whose
+// tiles are whole hold the same sum already, so the order depends only on n
+// and the item and block sizes.
+__device__ inline float vec_job_total(const float* partials, uint32_t count, uint32_t per_item) {
+  float s = 0.f;
+  for (uint32_t k = (threadIdx.x & 63u) * per_item; k < count; k += 64 * per_item) {
+    float v[kVecUnitsPerItem];
+#pragma unroll
+    for (int u = 0; u < kVecUnitsPerItem; ++u) v[u] = u < (int)per_item && k + u < count ? partials[k + u] : 0.f;
+    float item = v[0];
+#pragma unroll
+    for (int u = 1; u < kVecUnitsPerItem; ++u)
+      if (u < (int)per_item && k + u < count) item += v[u];
+    s += item;
+  }
+  return wave_total_f32(s);
+}
+#endif
 
 // BLOCK threads per block: 128, 256, 512 or 1024 (the template's block).
 template <int BLOCK>

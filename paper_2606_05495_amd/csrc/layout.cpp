@@ -153,7 +153,7 @@ static SlotLayout layout_of(const set_job_template& t) {
       L.out_cap = 64 + 4ull * t.batch_max;
       off = up(off + L.out_cap);
       L.scratch = off;
-      L.scratch_bytes = up(4ull * t.tiles_max) + kAlign;  // per-work-item partials, work counter
+      L.scratch_bytes = up(4ull * t.tiles_max) + kAlign;  // per-tile partials, work counter
       off = up(off + L.scratch_bytes);
       break;
     }

@@ -11,9 +11,9 @@
 //
 // Three launches on the caller's stream:
 //   plan   (one block): validate each job, pick its item size, prefix-sum the
-//          item counts into a descriptor table and rewind the work counter;
-//   items  (persistent grid): the batch pipeline's (job, item) kernel;
-//   totals (one thread per job): each job's item partials in item order.
+//          tile counts into a descriptor table and rewind the work counter;
+//   tiles  (persistent grid): the batch pipeline's (job, tile) kernel;
+//   totals (one wave per job): each job's tile partials in a fixed order.
 // A job's result depends only on (n, its item size), as on the batch path,
 // so both calls give bit-identical sums for the same jobs and tuning.
 #include <hip/hip_runtime.h>
@@ -55,11 +55,12 @@ namespace {
 struct NaPlanArgs {
   const set_vec_job* jobs;
   uint32_t count;
-  uint32_t pad;
+  uint32_t grid;       // blocks of the tile kernel
   uint64_t max_n;
   uint64_t pool_len;
   uint8_t* tab;
   uint32_t* work;
+  uint32_t split;           // a tile is a unit of a work item, not all of it
   uint32_t item_elems[64];  // elements per work item, per size bucket
 };
 
@@ -94,8 +95,11 @@ __device__ inline uint32_t block_excl_u32(uint32_t v, uint32_t* s_wave, uint32_t
 
 __global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(NaPlanArgs a) {
   __shared__ uint32_t s_wave[kNaPlanThreads / 64];
+  __shared__ unsigned long long s_elems;
   VecBatchDesc* D = reinterpret_cast<VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
   uint32_t carry = 0;
+  unsigned long long elems = 0;
+  if (threadIdx.x == 0) s_elems = 0;
   for (uint32_t base = 0; base < a.count; base += kNaPlanThreads) {
     const uint32_t j = base + threadIdx.x;
     VecBatchDesc d{};
@@ -104,38 +108,39 @@ __global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(NaPlanArgs 
       const bool ok = v.n >= 1 && v.n <= a.max_n && v.x_off <= a.pool_len && v.n <= a.pool_len - v.x_off &&
                       v.y_off <= a.pool_len && v.n <= a.pool_len - v.y_off;
       if (ok) {
-        const uint32_t te = a.item_elems[63 - __builtin_clzll(v.n)];
         d.x_off = v.x_off;
         d.y_off = v.y_off;
-        d.n = (uint32_t)v.n;
         d.a = v.a;
-        d.ntiles = (uint32_t)((v.n + te - 1) / te);
-        d.tile_elems = te;
+        vec_set_tiles(d, (uint32_t)v.n, a.item_elems[63 - __builtin_clzll(v.n)], kBlock, a.split != 0);
       }
     }
     uint32_t chunk_total;
     const uint32_t excl = block_excl_u32(d.ntiles, s_wave, &chunk_total);
     d.tile_start = carry + excl;
+    elems += d.n;
     if (j < a.count) D[j] = d;
     carry += chunk_total;
   }
+  atomicAdd(&s_elems, elems);  // cleared before the prefix's barriers
+  __syncthreads();
   if (threadIdx.x == 0) {
     VecBatchHdr* H = reinterpret_cast<VecBatchHdr*>(a.tab);
     H->count = a.count;
     H->total_tiles = carry;
+    H->claim = vec_claim(s_elems, carry, a.grid);
     *a.work = 0u;
   }
 }
 
-// Job j = thread j: NaN for a job the plan rejected (n == 0 in its
-// descriptor), else its item partials in item order.
+// Job j = wave j: NaN for a job the plan rejected (n == 0 in its descriptor),
+// else its tiles' partials in their fixed order.
 __global__ __launch_bounds__(kBlock) void k_vec_noalloc_totals(NaTotalsArgs a) {
   const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
   const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
-  const uint32_t j = blockIdx.x * kBlock + threadIdx.x;
+  const uint32_t j = blockIdx.x * kVecFinalJobs + (threadIdx.x >> 6);
   if (j >= H->count) return;
-  const VecBatchDesc d = D[j];
-  a.results[j] = d.n == 0 ? __builtin_nanf("") : vec_items_total(a.partials, d.tile_start, d.ntiles);
+  const float s = vec_job_total(a.partials + D[j].tile_start, D[j].ntiles, D[j].per_item);
+  if ((threadIdx.x & 63) == 0) a.results[j] = D[j].n == 0 ? __builtin_nanf("") : s;
 }
 
 std::mutex g_na_mu;
@@ -179,13 +184,14 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
   NaPlanArgs pa{};
   // Item size per bucket and the most items any job of length <= max_n needs.
   const int top = 63 - __builtin_clzll(max_n);
-  uint64_t worst = 0;
+  uint64_t worst = 0, worst_units = 0;
   for (int b = 0; b < 64; ++b) {
     const uint32_t te = (tuning && tuning->tile_elems[b]) ? tuning->tile_elems[b] : vec_default_tile(b);
     if (b <= top) {
       if (te == 0 || te % 1024 != 0) return na_fail(SET_EINVAL, "tile_elems must be a positive multiple of 1024");
       const uint64_t nmax = b == 63 ? max_n : std::min<uint64_t>(max_n, (2ull << b) - 1);
       worst = std::max<uint64_t>(worst, (nmax + te - 1) / te);
+      worst_units = std::max<uint64_t>(worst_units, vec_units(nmax, te, kBlock));
     }
     pa.item_elems[b] = te;
   }
@@ -211,13 +217,15 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     pa.pool_len = pool_len;
     pa.tab = tab;
     pa.work = work;
+    pa.split = count * worst_units <= kNaMaxItems;
+    pa.grid = grid ? grid : (uint32_t)kVecBatchGrid;
     hipLaunchKernelGGL(k_vec_noalloc_plan, dim3(1), dim3(kNaPlanThreads), 0, stream, pa);
     JobScalars js{};
     VecBatchArgs va{tab, x, y, partials, work, reinterpret_cast<DevSlotHdr*>(base + kNaHdrOff), js};
-    hipLaunchKernelGGL(k_vec_batch_tiles<kBlock>, dim3(grid ? grid : (unsigned)kVecBatchGrid), dim3(kBlock), 0, stream, va);
+    hipLaunchKernelGGL(k_vec_batch_tiles<kBlock>, dim3(pa.grid), dim3(kBlock), 0, stream, va);
     NaTotalsArgs ta{tab, partials, results};
-    hipLaunchKernelGGL(k_vec_noalloc_totals, dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream,
-                       ta);
+    hipLaunchKernelGGL(k_vec_noalloc_totals, dim3((unsigned)((count + kVecFinalJobs - 1) / kVecFinalJobs)), dim3(kBlock),
+                       0, stream, ta);
     e = hipGetLastError();
     if (e != hipSuccess) rc = na_fail(SET_EDEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
   }

@@ -947,6 +947,7 @@ class Context {
       uint32_t te, grid;
       std::vector<uint32_t> idx;
       uint32_t tiles;
+      uint64_t units;
     };
     std::vector<Plan> plans;
     for (int bk = 0; bk < 64; ++bk) {
@@ -954,16 +955,17 @@ class Context {
       uint32_t te = (tune && tune->tile_elems[bk]) ? tune->tile_elems[bk] : vec_default_tile(bk);
       uint32_t grid = (tune && tune->grid[bk]) ? tune->grid[bk] : (t.grid > 0 ? (uint32_t)t.grid : kVecBatchGrid);
       if (te % 1024 != 0 || grid < 1) return fail(SET_EINVAL, "tile_elems must be a positive multiple of 1024");
-      Plan cur{te, grid, {}, 0};
+      Plan cur{te, grid, {}, 0, 0};
       for (uint32_t i : buckets[bk]) {
         const uint64_t nt = (jobs[i].n + te - 1) / te;
         if (nt > t.tiles_max) return fail(SET_EINVAL, "a job needs more work items than tiles_max");
         if (cur.idx.size() >= t.batch_max || cur.tiles + nt > t.tiles_max) {
           plans.push_back(std::move(cur));
-          cur = Plan{te, grid, {}, 0};
+          cur = Plan{te, grid, {}, 0, 0};
         }
         cur.idx.push_back(i);
         cur.tiles += (uint32_t)nt;
+        cur.units += vec_units(jobs[i].n, te, vec_batch_block(t));
       }
       if (!cur.idx.empty()) plans.push_back(std::move(cur));
     }
@@ -998,21 +1000,21 @@ class Context {
       VecBatchHdr* H = reinterpret_cast<VecBatchHdr*>(tab);
       std::memset(H, 0, sizeof(*H));
       H->count = c;
-      H->total_tiles = pl.tiles;
       VecBatchDesc* D = reinterpret_cast<VecBatchDesc*>(tab + sizeof(VecBatchHdr));
       uint32_t ts = 0;
+      uint64_t elems = 0;
       for (uint32_t q = 0; q < c; ++q) {
         const set_vec_job& j = jobs[pl.idx[q]];
+        elems += j.n;
         D[q].x_off = j.x_off;
         D[q].y_off = j.y_off;
-        D[q].n = (uint32_t)j.n;
         D[q].a = j.a;
         D[q].tile_start = ts;
-        D[q].ntiles = (uint32_t)((j.n + pl.te - 1) / pl.te);
-        D[q].tile_elems = pl.te;
-        D[q].pad[0] = D[q].pad[1] = D[q].pad[2] = 0;
+        vec_set_tiles(D[q], (uint32_t)j.n, pl.te, vec_batch_block(t), pl.units <= t.tiles_max);
         ts += D[q].ntiles;
       }
+      H->total_tiles = ts;
+      H->claim = vec_claim(elems, ts, pl.grid);
       set_job_args a;
       std::memset(&a, 0, sizeof(a));
       a.host_in = tab;
@@ -1048,6 +1050,7 @@ class Context {
     const set_job_template& t = templates[S.vtmpl];
     while (true) {
       int r = -1;
+      uint64_t units = 0;  // of the requests taken
       std::vector<uint32_t> take;
       {
         std::unique_lock<std::mutex> lk(S.mu);
@@ -1072,6 +1075,7 @@ class Context {
           const uint64_t nt = (a.n + te - 1) / te;
           if (!take.empty() && tiles + nt > t.tiles_max) break;
           tiles += nt;
+          units += vec_units(a.n, te, vec_batch_block(t));
           take.push_back(S.pending.front());
           S.pending.pop_front();
         }
@@ -1084,22 +1088,22 @@ class Context {
       std::memset(H, 0, sizeof(*H));
       VecBatchDesc* D = reinterpret_cast<VecBatchDesc*>(R.tab + sizeof(VecBatchHdr));
       uint32_t ts = 0;
+      uint64_t elems = 0;
       for (size_t q = 0; q < take.size(); ++q) {
         const set_job_args& a = S.reqs[take[q]].args;
+        elems += a.n;
         const int bk = 63 - __builtin_clzll(a.n);
         const uint32_t te = (S.tuning && S.tuning->tile_elems[bk]) ? S.tuning->tile_elems[bk] : vec_default_tile(bk);
         D[q].x_off = a.x_off;
         D[q].y_off = a.y_off;
-        D[q].n = (uint32_t)a.n;
         D[q].a = a.a;
         D[q].tile_start = ts;
-        D[q].ntiles = (uint32_t)((a.n + te - 1) / te);
-        D[q].tile_elems = te;
-        D[q].pad[0] = D[q].pad[1] = D[q].pad[2] = 0;
+        vec_set_tiles(D[q], (uint32_t)a.n, te, vec_batch_block(t), units <= t.tiles_max);
         ts += D[q].ntiles;
       }
       H->count = (uint32_t)take.size();
       H->total_tiles = ts;
+      H->claim = vec_claim(elems, ts, t.grid > 0 ? (uint32_t)t.grid : (uint32_t)kVecBatchGrid);
       set_job_args b;
       std::memset(&b, 0, sizeof(b));
       b.host_in = R.tab;
