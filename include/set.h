@@ -176,7 +176,7 @@ enum set_pipeline {
     /* Iterative thermal grid (a memory-bound iterative workload like the
      * paper's Hotspot, Section 5.1): in = temperature grid T0 followed by
      * the power grid P (each height x width float32, row-major); max_n = the
-     * number of explicit steps K (1..32), each one kernel of the chain:
+     * number of explicit steps K (1..32), one or several to a kernel of the chain:
      *   T' = T + 0.5*P + 0.1*(N + S - 2T) + 0.1*(W + E - 2T) + (300 - T)/640
      * with N, S, W, E the four neighbours and a neighbour outside the grid
      * taken as the cell itself (no heat crosses the border); then a kernel

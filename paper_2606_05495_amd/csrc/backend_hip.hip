@@ -848,19 +848,24 @@ class HipBackend : public Backend {
         break;
       }
       case SET_PIPE_HOTSPOT_F32: {
-        // step k reads T_k and writes T_{k+1}: T_0 is the input, the last
-        // step writes the output payload, the others alternate b1 / b2
+        // launch 0 reads the input, the last launch writes the output payload,
+        // the others alternate b1 / b2
         const int K = (int)t.max_n;
         const float* P = (const float*)(b + L.in) + (size_t)h * w;
         const void* hk = !image_window_path(w)  ? (const void*)&k_hotspot_f32
                          : window_full_width(w) ? (const void*)&k_hotspot_win_f32<true>
                                                 : (const void*)&k_hotspot_win_f32<false>;
-        for (int k = 0; k < K; ++k) {
-          const float* src = (k == 0) ? (const float*)(b + L.in) : sl.hot[k - 1].tout;
-          float* dst = (k == K - 1) ? (float*)(b + L.out + 64) : (float*)(b + ((k % 2 == 0) ? L.b1 : L.b2));
-          sl.hot[k] = HotspotArgs{src, P, dst, h, w, k == 0 ? 1 : 0, sc.hdr, JobScalars{}};
-          const int hr = hotspot_band_rows(h, w);
-          if (hr)
+        const void* mks[4] = {(const void*)&k_hotspot_steps_f32<1>, (const void*)&k_hotspot_steps_f32<2>,
+                              (const void*)&k_hotspot_steps_f32<3>, (const void*)&k_hotspot_steps_f32<4>};
+        const int L = hotspot_launches(h, w, K);
+        for (int k = 0; k < L; ++k) {
+          const float* src = (k == 0) ? (const float*)(b + p.L.in) : sl.hot[k - 1].tout;
+          float* dst = (k == L - 1) ? (float*)(b + p.L.out + 64) : (float*)(b + ((k % 2 == 0) ? p.L.b1 : p.L.b2));
+          const int n = hotspot_steps(h, w, K, k), hr = hotspot_band_rows(h, w);
+          sl.hot[k] = HotspotArgs{src, P, dst, h, w, k == 0 ? 1 : 0, n, sc.hdr, JobScalars{}};
+          if (n > 1)
+            stage(mks[hotspot_halo(n) - 1], to_dim3(hotspot_steps_grid(h, w, hotspot_halo(n))), &sl.hot[k]);
+          else if (hr)
             stage(hr == 16 ? (const void*)&k_hotspot_band_f32<16> : (const void*)&k_hotspot_band_f32<8>,
                   to_dim3(hotspot_grid(h, w)), &sl.hot[k], (unsigned)kBandCols / 4);
           else

@@ -523,6 +523,14 @@ void k_hotspot_band_f32(HotspotArgs a) {
 }
 template void k_hotspot_band_f32<8>(HotspotArgs);
 template void k_hotspot_band_f32<16>(HotspotArgs);
+template <int HALO>
+void k_hotspot_steps_f32(HotspotArgs a) {
+  if (a.first) stamp(a.hdr, a.js);
+}
+template void k_hotspot_steps_f32<1>(HotspotArgs);
+template void k_hotspot_steps_f32<2>(HotspotArgs);
+template void k_hotspot_steps_f32<3>(HotspotArgs);
+template void k_hotspot_steps_f32<4>(HotspotArgs);
 void k_hotspot_f32(HotspotArgs a) {
   if (a.first) stamp(a.hdr, a.js);
 }
@@ -587,6 +595,10 @@ struct Register {
     register_kernel(&k_hotspot_win_f32<true>);
     register_kernel(&k_hotspot_win_f32<false>);
     register_kernel(&k_hotspot_f32);
+    register_kernel(&k_hotspot_steps_f32<1>);
+    register_kernel(&k_hotspot_steps_f32<2>);
+    register_kernel(&k_hotspot_steps_f32<3>);
+    register_kernel(&k_hotspot_steps_f32<4>);
     register_kernel(&k_hotspot_band_f32<8>);
     register_kernel(&k_hotspot_band_f32<16>);
     register_kernel(&k_box3_u8_u16);

@@ -85,6 +85,8 @@ __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > 
 // 10.15 us at 2048x2048; the next stage, which reads them, did not slow
 // (thermal jobs of 16 steps ran at the same rate either way).
 typedef float v4f_t __attribute__((ext_vector_type(4)));
+// Four floats at any float's address: gfx950 moves 16 bytes at 4-byte alignment.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef long long v2i64_t __attribute__((ext_vector_type(2)));
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 __device__ inline void store_nt(float* p, float x, float y, float z, float w) {
@@ -414,6 +416,14 @@ __device__ inline float from_left(float v, float edge) {
 }
 __device__ inline float from_right(float v, float edge) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
+// The same shifts within rows of 16 lanes (DPP row_shr:1 / row_shl:1).
+__device__ inline float row_from_left(float v, float edge) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x111, 0xf, 0xf, false));
+}
+__device__ inline float row_from_right(float v, float edge) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x101, 0xf, 0xf, false));
 }
 
 __device__ inline uint32_t wave_total_u32(uint32_t v) {
@@ -867,6 +877,93 @@ template __global__ void k_hotspot_band_f32<16>(HotspotArgs a);
 template __global__ void k_hotspot_win_f32<true>(HotspotArgs a);
 template __global__ void k_hotspot_win_f32<false>(HotspotArgs a);
 
+// Several steps in one launch.  A block holds a tile of 64 x 64 cells in
+// registers (16 lanes of 4 columns by 16 groups of 4 rows: a group is a DPP
+// row, so the left and right neighbours are lane shifts) and passes the groups'
+// outer rows through LDS, one barrier a step.  What lies S = 4 HALO cells
+// inside the tile's edge is right after up to S steps and is stored; tiles
+// overlap by 2 S.  Cells beyond the grid are loaded as its mirror image: no heat
+// crosses the border, so the image takes the same steps as the cells it
+// mirrors, bit for bit (w + e and n + s commute), and the steps know no border.
+// The cells' arithmetic is the one-step kernels'.
+// On a small grid a step is launch and memory latency, and 16 steps in one
+// launch take about the time of two of one step; on a large one a launch is
+// bound by the vector ALU (9 instructions a cell and step, 1.8 cells computed
+// for each stored at S = 8) where one step was bound by memory.  64 jobs of
+// 256^2 and 16 steps: 1630 -> 1200 us; one of 1500 x 2000 and 32: 947 -> 794.
+__device__ inline int mirror_index(int i, int n) {  // i any distance outside [0, n)
+  if ((unsigned)i < (unsigned)n) return i;
+  i = i < 0 ? -1 - i : i;
+  if (i >= 2 * n) i %= 2 * n;  // tiles wider than the grid only
+  return i < n ? i : 2 * n - 1 - i;
+}
+template <int HALO>
+__global__ __launch_bounds__(kBlock) void k_hotspot_steps_f32(HotspotArgs a) {
+  constexpr int R = 4, G = kBlock / 16, S = 4 * HALO, U = kHotTile - 2 * S;
+  static_assert(G * R == kHotTile && 16 * 4 == kHotTile, "square tile");
+  unsigned bx, by;
+  xcd_tile(bx, by);
+  if (a.first && bx == 0 && by == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  __shared__ v4f_t s_top[2][G][16], s_bottom[2][G][16];
+  const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int x = (int)bx * U - S + 4 * lane, y = (int)by * U - S + R * grp;
+  size_t row[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) row[r] = (size_t)mirror_index(y + r, a.h) * a.w;
+  v4f_t v[R], p[R];
+  if (x >= 0 && x + 4 <= a.w) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      v[r] = *reinterpret_cast<const v4f_any*>(a.tin + row[r] + x);
+      p[r] = *reinterpret_cast<const v4f_any*>(a.p + row[r] + x);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = mirror_index(x + j, a.w);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        v[r][j] = a.tin[row[r] + c];
+        p[r][j] = a.p[row[r] + c];
+      }
+    }
+  }
+  const int above = grp > 0 ? grp - 1 : 0, below = grp < G - 1 ? grp + 1 : G - 1;
+  for (int k = 0; k < a.steps; ++k) {
+    const int b = k & 1;
+    s_top[b][grp][lane] = v[0];
+    s_bottom[b][grp][lane] = v[R - 1];
+    __syncthreads();
+    v4f_t up = s_bottom[b][above][lane];
+    const v4f_t down = s_top[b][below][lane];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const v4f_t t = v[r], s = r + 1 < R ? v[r + 1] : down;
+      const float c[6] = {row_from_left(t.w, t.x), t.x, t.y, t.z, t.w, row_from_right(t.x, t.w)};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[r][j] = hotspot::step(c[j + 1], p[r][j], up[j], s[j], c[j], c[j + 2]);
+      up = t;
+    }
+  }
+  if (lane < HALO || lane >= 16 - HALO || grp < HALO || grp >= G - HALO) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (y + r >= a.h) break;
+    float* o = a.tout + (size_t)(y + r) * a.w + x;
+    if (x + 4 <= a.w) {
+      *reinterpret_cast<v4f_any*>(o) = v[r];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (x + j < a.w) o[j] = v[r][j];
+    }
+  }
+}
+template __global__ void k_hotspot_steps_f32<1>(HotspotArgs a);
+template __global__ void k_hotspot_steps_f32<2>(HotspotArgs a);
+template __global__ void k_hotspot_steps_f32<3>(HotspotArgs a);
+template __global__ void k_hotspot_steps_f32<4>(HotspotArgs a);
+
 // Widths that are not a multiple of 4: one cell per thread.
 __global__ __launch_bounds__(kBlock) void k_hotspot_f32(HotspotArgs a) {
   if (a.first && blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
@@ -959,10 +1056,6 @@ __device__ inline float tanh_f32(float z) {
   const float big = copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(e + 1.f), 1.f), z);
   return fabsf(z) >= 0.8f ? big : small;
 }
-
-// Four floats at any float's address: gfx950 loads 16 bytes from 4-byte
-// aligned addresses, so windows at every offset take the same path.
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Thread's share of sum tanh(a*x + y) over len elements, by a block of BLOCK
 // threads: thread j takes the 4-element groups j, j + BLOCK, ... in order, and

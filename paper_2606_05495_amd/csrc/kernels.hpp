@@ -188,18 +188,21 @@ __global__ void k_job_end(JobEndArgs a);
 // stream st (lib_scan.hip).  With ws == nullptr only ws_bytes is computed.
 hipError_t lib_scan(void* ws, size_t& ws_bytes, const int32_t* in, int64_t* out, size_t n, hipStream_t st);
 
-// One explicit step of the thermal grid: tout = step(tin, p).  The first
-// step of a job (first != 0) also writes the job's scalars into the slot
-// header.
+// Explicit steps of the thermal grid: tout = tin after `steps` of them (1 in
+// the one-step kernels).  The first launch of a job (first != 0) also writes
+// the job's scalars into the slot header.
 struct HotspotArgs {
   const float* tin;
   const float* p;
   float* tout;
   int h, w;
   int first;
+  int steps;
   DevSlotHdr* hdr;
   JobScalars js;
 };
+template <int HALO>
+__global__ void k_hotspot_steps_f32(HotspotArgs a);
 template <bool FULL>
 __global__ void k_hotspot_win_f32(HotspotArgs a);
 template <int R>

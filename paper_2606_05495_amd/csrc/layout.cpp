@@ -317,8 +317,9 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
       stage("vec_batch_final", 64 + 48ull * t.batch_max + 4ull * t.tiles_max + 4ull * t.batch_max);
       break;
     case SET_PIPE_HOTSPOT_F32:
-      // each step reads T and P and writes T'
-      for (uint64_t k = 0; k < t.max_n; ++k) stage("hotspot_step_f32", 12 * npix);
+      // each launch (of one or more steps) reads T and P and writes T'
+      for (int k = 0; k < hotspot_launches((int)t.height, (int)t.width, (int)t.max_n); ++k)
+        stage("hotspot_step_f32", 12 * npix);
       stage("job_end", 64 + 64);
       break;
     case SET_PIPE_SCAN_LIB_I32_I64:

@@ -145,6 +145,31 @@ inline Grid3 hotspot_grid(int h, int w) {
   const uint64_t n = (uint64_t)h * w;
   return {(unsigned)((n + kBlock - 1) / kBlock), 1u, 1u};
 }
+// Steps of a job that one launch takes (k_hotspot_steps_f32): up to 16 on grids
+// of 512^2 cells or fewer, 8 above; K steps are dealt evenly over the launches,
+// and a launch of one step takes the one-step kernels.  The tile's halo is the
+// steps rounded up to 4 cells.  On a small grid a launch is latency and more
+// steps cost little; on a large one the halo's cells are computed for nothing
+// (3 of 4 at 16 steps).  One job, us from submit to drained, at 1 (the one-step
+// kernels) / 4 / 8 / 16 steps a launch: 256^2, K = 16: 101 / 96 / 91 / 79;
+// 512^2, K = 16: 153 / 135 / 128 / 125; 1024^2, K = 16: 344 / 317 / 311 / 320;
+// 1500 x 2000, K = 32: 947 / 803 / 794 / 841; 4096^2, K = 16: 4217 / 3837 /
+// 3825 / 3971.
+constexpr int kHotTile = 64;
+inline int hotspot_steps_max(int h, int w) { return (int64_t)h * w <= (int64_t)512 * 512 ? 16 : 8; }
+inline int hotspot_launches(int h, int w, int K) {
+  const int m = hotspot_steps_max(h, w);
+  return (K + m - 1) / m;
+}
+inline int hotspot_steps(int h, int w, int K, int launch) {
+  const int n = hotspot_launches(h, w, K);
+  return K / n + (launch < K % n ? 1 : 0);
+}
+inline int hotspot_halo(int steps) { return (steps + 3) / 4; }
+inline Grid3 hotspot_steps_grid(int h, int w, int halo) {
+  const int u = kHotTile - 8 * halo;
+  return {(unsigned)((w + u - 1) / u), (unsigned)((h + u - 1) / u), 1u};
+}
 // Vector job: blocks for length n.  Deterministic in n, so the reduction
 // order of a job depends only on its length.
 SETRT_HD inline unsigned vec_blocks(uint64_t n) {

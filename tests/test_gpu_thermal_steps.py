@@ -1,0 +1,44 @@
+"""Thermal jobs whose steps are taken several to a launch: grids smaller than a
+tile's halo, a cell either side of a tile's edge, and step counts around those
+where the launches and the halo change."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_05495_amd import synth
+from paper_2606_05495_amd.runtime import Context, pinned
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (1, 40), (40, 1), (2, 3), (15, 16), (17, 15), (32, 32), (33, 31), (47, 49),
+                                   (49, 65), (57, 112), (64, 113), (512, 512), (511, 514), (700, 771)])
+def test_steps_per_launch(torch_gpu, shape):
+    """Against the float64 oracle within the bound its docstring derives."""
+    h, w = shape
+    print("steps per launch", shape)
+    sys.stdout.flush()
+    t0, p = synth.hotspot_input(6, h * 1000 + w, h, w)
+    ib, ob = 8 * h * w, 64 + 4 * h * w
+    tin, nin = pinned(ib)
+    tout, nout = pinned(ob)
+    nin[:].view(np.float32)[:] = np.concatenate([t0.ravel(), p.ravel()])
+    for steps in (2, 4, 5, 8, 9, 12, 13, 16, 17, 31, 32):
+        with Context(mode="sync", workers=1, slots=1) as ctx:
+            tid = ctx.define("hotspot", width=w, height=h, max_n=steps)
+            nout[:] = 0
+            ctx.submit(tid, host_in=tin.data_ptr(), in_bytes=ib, host_out=tout.data_ptr(), out_bytes=ob)
+            ctx.drain()
+        got = nout[64:].view(np.float32).reshape(h, w)
+        ref = oracle.hotspot(t0, p, steps)
+        assert np.max(np.abs(got - ref)) <= oracle.hotspot_tolerance(ref, steps), (shape, steps)
