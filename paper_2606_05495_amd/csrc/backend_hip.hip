@@ -47,6 +47,7 @@ struct Slot {
   char* base = nullptr;
   int tmpl = 0, w = 0, s = 0;
   BoxArgs box;
+  BoxHistArgs boxh;
   Div9Args div;
   HistArgs hist;
   HistFinalArgs histf;
@@ -422,7 +423,9 @@ class HipBackend : public Backend {
       if (i == 1) HIPCK(library_stage(p, sl, st));
       HIPCK(hipLaunchKernel(sl.func[i], sl.grid[i], dim3(sl.block[i]), sl.argv[i], 0, st));
     }
-    if (out_by_kernel(p.t)) {
+    if (writes_out(p.t)) {
+      // the last stage did
+    } else if (out_by_kernel(p.t)) {
       sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
       HIPCK(hipLaunchKernel((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), sl.d2h_argv, 0, st));
     } else {
@@ -575,6 +578,7 @@ class HipBackend : public Backend {
         return hipMemcpyAsync(sl.base + p.L.in, p.placeholder, in_b, hipMemcpyHostToDevice, st);
       }
       if (copy_out) {
+        if (writes_out(p.t)) return hipSuccess;  // part of the last stage
         if (out_by_kernel(p.t)) {
           CopyArgs ca{sl.base + p.L.out, p.placeholder, out_b};
           void* av[1] = {&ca};
@@ -585,6 +589,9 @@ class HipBackend : public Backend {
       if (lib_call) return library_stage(p, sl, st);
       return hipLaunchKernel(sl.func[ks], sl.grid[ks], dim3(sl.block[ks]), sl.argv[ks], 0, st);
     };
+    // the jobs' own output buffers may be gone by now
+    if (writes_out(p.t))
+      for (Slot& s : p.slots) set_out(s, p.t.pipeline, p.placeholder);
     hipEvent_t e0, e1;
     HIPCK(hipEventCreate(&e0));
     HIPCK(hipEventCreate(&e1));
@@ -769,6 +776,13 @@ class HipBackend : public Backend {
     sc.outh = reinterpret_cast<set_out_header*>(b + L.out);
     sc.canary_head = canary_value(sl.tmpl, sl.w, sl.s, 0);
     sc.canary_tail = canary_value(sl.tmpl, sl.w, sl.s, 1);
+    // A stage that writes the output to host memory starts out on the
+    // placeholder, like the copies; it stores the completion word itself
+    // unless the slot is poisoned after it.
+    const bool wo = writes_out(p.t);
+    if (wo) sc.outh = reinterpret_cast<set_out_header*>(p.placeholder);
+    sc.word = wo && flag_in_stage(p) ? p.words + ((size_t)sl.w * d_ + sl.s) * 8 : nullptr;
+    char* const payload = reinterpret_cast<char*>(sc.outh) + 64;
     const set_job_template& t = p.t;
     const int h = (int)t.height, w = (int)t.width;
     const int64_t npix = (int64_t)h * w;
@@ -782,11 +796,19 @@ class HipBackend : public Backend {
     sl.nstages = 0;
     switch (t.pipeline) {
       case SET_PIPE_BOX_HIST_U8: {
+        if (!(t.flags & SET_TF_DEBUG)) {
+          const unsigned bb = box_hist_blocks(h, w);
+          sl.boxh = BoxHistArgs{(const uint8_t*)(b + L.in), h, w, (uint32_t*)(b + L.scratch), sc.hdr, JobScalars{}};
+          sl.histf = HistFinalArgs{(const uint32_t*)(b + L.scratch), bb, (uint32_t*)payload, sc};
+          stage((const void*)&k_box_hist_u8, dim3(bb), &sl.boxh);
+          stage(wo ? (const void*)&k_copy_out_hist256 : (const void*)&k_hist256_final, dim3(1), &sl.histf);
+          break;
+        }
         const unsigned hb = hist_blocks(npix);
         sl.box = BoxArgs{(const uint8_t*)(b + L.in), (uint16_t*)(b + L.b1), h, w, sc.hdr, JobScalars{}};
         sl.div = Div9Args{(const uint16_t*)(b + L.b1), (uint8_t*)(b + L.b2), npix};
         sl.hist = HistArgs{(const uint8_t*)(b + L.b2), npix, (uint32_t*)(b + L.scratch)};
-        sl.histf = HistFinalArgs{(const uint32_t*)(b + L.scratch), hb, (uint32_t*)(b + L.out + 64), sc};
+        sl.histf = HistFinalArgs{(const uint32_t*)(b + L.scratch), hb, (uint32_t*)payload, sc};
         stage((const void*)&k_box3_u8_u16, to_dim3(box_grid(h, w)), &sl.box);
         stage((const void*)&k_div9_u16_u8, dim3(div9_blocks(npix)), &sl.div);
         stage((const void*)&k_hist256_u8, dim3(hb), &sl.hist);
@@ -803,7 +825,7 @@ class HipBackend : public Backend {
                              t.threshold != 0.f ? t.threshold : 1.0f, (uint32_t*)(b + L.scratch),
                              (float*)(b + L.scratch + q)};
         sl.sobelf = SobelFinalArgs{(const uint32_t*)(b + L.scratch), (const float*)(b + L.scratch + q), nb,
-                                   (uint32_t*)(b + L.out + 64), (float*)(b + L.out + 68), sc};
+                                   (uint32_t*)payload, (float*)(payload + 4), sc};
         const bool win = image_window_path(w), full = window_full_width(w);
         const int gr = gauss_win_rows(h, w), sr = sobel_win_rows(h, w);
         // window kernels by rows per wave (2 or 4) and full-width variant
@@ -820,15 +842,15 @@ class HipBackend : public Backend {
           stage(gk, to_dim3(gauss_grid(h, w)), &sl.gauss);
         const void* sk = win ? sks[sr == 2 ? 0 : 1][full ? 1 : 0] : (const void*)&k_sobel_thresh_f32;
         stage(sk, to_dim3(sg), &sl.sobel);
-        stage((const void*)&k_sobel_final, dim3(1), &sl.sobelf);
+        stage(wo ? (const void*)&k_copy_out_sobel : (const void*)&k_sobel_final, dim3(1), &sl.sobelf);
         break;
       }
       case SET_PIPE_SAXPY_TANH_SUM_F32: {
         sl.vec = VecArgs{t.dev_x_pool, t.dev_y_pool, (float*)(b + L.scratch), sc.hdr, JobScalars{}};
         sl.vec.js.n = t.max_n;
-        sl.vecf = VecFinalArgs{(const float*)(b + L.scratch), (float*)(b + L.out + 64), sc};
+        sl.vecf = VecFinalArgs{(const float*)(b + L.scratch), (float*)payload, sc};
         stage((const void*)&k_saxpy_tanh_sum_f32, dim3(vec_blocks(t.max_n)), &sl.vec);
-        stage((const void*)&k_vec_final, dim3(1), &sl.vecf);
+        stage(wo ? (const void*)&k_copy_out_vec : (const void*)&k_vec_final, dim3(1), &sl.vecf);
         break;
       }
       case SET_PIPE_SAXPY_BATCH_F32: {
@@ -907,6 +929,28 @@ class HipBackend : public Backend {
     sl.delay = DelayArgs{us * clock_khz_ / 1000, 8 * us + 64};
   }
 
+  // Point a last stage that writes the job's output itself at `out`.
+  void set_out(Slot& sl, int pipeline, void* out) {
+    char* o = static_cast<char*>(out);
+    set_out_header* h = static_cast<set_out_header*>(out);
+    switch (pipeline) {
+      case SET_PIPE_BOX_HIST_U8:
+        sl.histf.sc.outh = h;
+        sl.histf.H = reinterpret_cast<uint32_t*>(o + 64);
+        break;
+      case SET_PIPE_GAUSS_SOBEL_F32:
+        sl.sobelf.sc.outh = h;
+        sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
+        sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
+        break;
+      case SET_PIPE_SAXPY_TANH_SUM_F32:
+        sl.vecf.sc.outh = h;
+        sl.vecf.out_sum = reinterpret_cast<float*>(o + 64);
+        break;
+    }
+  }
+  // The last stage stores the completion word: nothing follows it in the graph.
+  bool flag_in_stage(const Pipe& p) const { return p.words && writes_out(p.t) && !poisons(p); }
   static bool poisons(const Pipe& p) { return (p.t.flags & SET_TF_POISON) != 0; }
   static bool delays(const Pipe& p) { return p.t.stress_delay_us > 0; }
   static unsigned poison_blocks(const Pipe& p) {
@@ -943,7 +987,10 @@ class HipBackend : public Backend {
     js.a = j->args.a;
     switch (p.t.pipeline) {
       case SET_PIPE_BOX_HIST_U8:
-        sl.box.js = js;
+        if (p.t.flags & SET_TF_DEBUG)
+          sl.box.js = js;
+        else
+          sl.boxh.js = js;
         break;
       case SET_PIPE_GAUSS_SOBEL_F32:
         sl.gauss.js = js;
@@ -974,6 +1021,7 @@ class HipBackend : public Backend {
     sl.in_bytes = pipeline_in_bytes(p.t, js.n);
     sl.host_out = j->args.host_out;
     sl.out_bytes = pipeline_out_bytes(p.t, js.n);
+    if (writes_out(p.t)) set_out(sl, p.t.pipeline, sl.host_out);
   }
 
   hipKernelNodeParams kparams(Slot& sl, int i) {
@@ -1062,7 +1110,9 @@ class HipBackend : public Backend {
       HIPCK(hipGraphAddKernelNode(&cn->k[i], g, prev ? &prev : nullptr, prev ? 1 : 0, &kp));
       prev = cn->k[i];
     }
-    if (out_by_kernel(p.t)) {
+    if (writes_out(p.t)) {
+      // the last stage does
+    } else if (out_by_kernel(p.t)) {
       sl.d2h_copy = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
       hipKernelNodeParams kp = copy_params(sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
       HIPCK(hipGraphAddKernelNode(&cn->d2h, g, &prev, 1, &kp));
@@ -1070,13 +1120,13 @@ class HipBackend : public Backend {
       HIPCK(hipGraphAddMemcpyNode1D(&cn->d2h, g, &prev, 1, p.placeholder, sl.base + p.L.out, p.L.out_cap,
                                     hipMemcpyDeviceToHost));
     }
-    prev = cn->d2h;
+    if (cn->d2h) prev = cn->d2h;
     if (poisons(p)) {
       hipKernelNodeParams kp = stress_params(p, sl, true);
       HIPCK(hipGraphAddKernelNode(&cn->poison, g, &prev, 1, &kp));
       prev = cn->poison;
     }
-    if (p.words && g == sl.graph) {
+    if (p.words && !flag_in_stage(p) && g == sl.graph) {
       hipKernelNodeParams kf = flag_params(sl);
       HIPCK(hipGraphAddKernelNode(&cn->flag, g, &prev, 1, &kf));
     }
@@ -1114,21 +1164,25 @@ class HipBackend : public Backend {
       if (i == 1) HIPCK(library_stage(p, sl, st));
       HIPCK(hipLaunchKernel(sl.func[i], sl.grid[i], dim3(sl.block[i]), sl.argv[i], 0, st));
     }
-    if (out_by_kernel(p.t)) {
+    if (writes_out(p.t)) {
+      // the last stage does
+    } else if (out_by_kernel(p.t)) {
       sl.d2h_copy = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
       HIPCK(hipLaunchKernel((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), sl.d2h_argv, 0, st));
     } else {
       HIPCK(hipMemcpyAsync(p.placeholder, sl.base + p.L.out, p.L.out_cap, hipMemcpyDeviceToHost, st));
     }
     if (poisons(p)) HIPCK(launch_stress(p, sl, true, st));
-    if (p.words) HIPCK(hipLaunchKernel((const void*)&k_done_flag, dim3(1), dim3(64), sl.flag_argv, 0, st));
+    const bool flag_node = p.words && !flag_in_stage(p);
+    if (flag_node) HIPCK(hipLaunchKernel((const void*)&k_done_flag, dim3(1), dim3(64), sl.flag_argv, 0, st));
     HIPCK(hipStreamEndCapture(st, out));
     size_t n = 0;
     HIPCK(hipGraphGetNodes(*out, nullptr, &n));
     std::vector<hipGraphNode_t> nodes(n);
     HIPCK(hipGraphGetNodes(*out, nodes.data(), &n));
     const size_t fixed =
-        (in_node ? 1 : 0) + (delays(p) ? 1 : 0) + sl.nstages + 1 + (poisons(p) ? 1 : 0) + (p.words ? 1 : 0);
+        (in_node ? 1 : 0) + (delays(p) ? 1 : 0) + sl.nstages + (writes_out(p.t) ? 0 : 1) + (poisons(p) ? 1 : 0) +
+        (flag_node ? 1 : 0);
     const size_t lib_nodes = n - std::min(n, fixed);  // captured library kernels between stages 0 and 1
     if (n < fixed || (lib_template(p.t) ? lib_nodes < 1 : lib_nodes != 0)) {
       if (err) *err = "captured graph has an unexpected number of nodes";
@@ -1181,9 +1235,9 @@ class HipBackend : public Backend {
       }
       cn->k[i] = order[k++];
     }
-    cn->d2h = order[k++];
+    if (!writes_out(p.t)) cn->d2h = order[k++];
     if (poisons(p)) cn->poison = order[k++];
-    if (p.words) cn->flag = order[k];
+    if (flag_node) cn->flag = order[k];
     return SET_OK;
   }
 
@@ -1209,7 +1263,10 @@ class HipBackend : public Backend {
         HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[i], &kd));
       }
     }
-    if (out_by_kernel(p.t)) {
+    if (writes_out(p.t)) {
+      hipKernelNodeParams kd = kparams(sl, sl.nstages - 1);
+      HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[sl.nstages - 1], &kd));
+    } else if (out_by_kernel(p.t)) {
       sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
       hipKernelNodeParams kd = copy_params(sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
       HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.d2h, &kd));

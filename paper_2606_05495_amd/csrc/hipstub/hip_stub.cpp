@@ -495,6 +495,7 @@ void publish(const SlotConst& sc) {
   o->canary_ok = canaries ? 1u : 0u;
   o->reserved[0] = o->reserved[1] = o->reserved[2] = 0;
   o->magic = SET_OUT_MAGIC;
+  if (sc.word) __atomic_store_n(sc.word, h->seq, __ATOMIC_RELEASE);
 }
 }  // namespace
 
@@ -537,7 +538,9 @@ void k_hotspot_f32(HotspotArgs a) {
 void k_box3_u8_u16(BoxArgs a) { stamp(a.hdr, a.js); }
 void k_div9_u16_u8(Div9Args) {}
 void k_hist256_u8(HistArgs) {}
+void k_box_hist_u8(BoxHistArgs a) { stamp(a.hdr, a.js); }
 void k_hist256_final(HistFinalArgs a) { publish(a.sc); }
+void k_copy_out_hist256(HistFinalArgs a) { publish(a.sc); }
 void k_gauss5_f32(GaussArgs a) { stamp(a.hdr, a.js); }
 template <int R, bool FULL>
 void k_gauss5_win_f32(GaussArgs a) {
@@ -561,8 +564,10 @@ template void k_sobel_thresh_win_f32<2, false>(SobelArgs);
 template void k_sobel_thresh_win_f32<4, true>(SobelArgs);
 template void k_sobel_thresh_win_f32<4, false>(SobelArgs);
 void k_sobel_final(SobelFinalArgs a) { publish(a.sc); }
+void k_copy_out_sobel(SobelFinalArgs a) { publish(a.sc); }
 void k_saxpy_tanh_sum_f32(VecArgs a) { stamp(a.hdr, a.js); }
 void k_vec_final(VecFinalArgs a) { publish(a.sc); }
+void k_copy_out_vec(VecFinalArgs a) { publish(a.sc); }
 template <int BLOCK>
 void k_vec_batch_tiles(VecBatchArgs a) {
   stamp(a.hdr, a.js);
@@ -604,7 +609,9 @@ struct Register {
     register_kernel(&k_box3_u8_u16);
     register_kernel(&k_div9_u16_u8);
     register_kernel(&k_hist256_u8);
+    register_kernel(&k_box_hist_u8);
     register_kernel(&k_hist256_final);
+    register_kernel(&k_copy_out_hist256);
     register_kernel(&k_gauss5_f32);
     register_kernel(&k_gauss5_win_f32<2, true>);
     register_kernel(&k_gauss5_win_f32<2, false>);
@@ -618,8 +625,10 @@ struct Register {
     register_kernel(&k_sobel_thresh_win_f32<4, true>);
     register_kernel(&k_sobel_thresh_win_f32<4, false>);
     register_kernel(&k_sobel_final);
+    register_kernel(&k_copy_out_sobel);
     register_kernel(&k_saxpy_tanh_sum_f32);
     register_kernel(&k_vec_final);
+    register_kernel(&k_copy_out_vec);
     register_kernel(&k_vec_batch_tiles<128>);
     register_kernel(&k_vec_batch_tiles<256>);
     register_kernel(&k_vec_batch_tiles<512>);

@@ -138,6 +138,14 @@ struct TemplateSizes {
   char stage_names[kMaxStages][32];
 };
 
+// Templates whose last stage, a kernel of one block, writes the job's output to
+// host memory itself: small outputs without intermediate images, of copy modes
+// whose output copy is a kernel.
+inline bool writes_out(const set_job_template& t) {
+  return t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG) &&
+         (t.pipeline == SET_PIPE_BOX_HIST_U8 || t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 ||
+          t.pipeline == SET_PIPE_SAXPY_TANH_SUM_F32);
+}
 // Static per-job sizes of a template (in/out bytes for a job with length n).
 uint64_t pipeline_in_bytes(const set_job_template& t, uint64_t n);
 uint64_t pipeline_out_bytes(const set_job_template& t, uint64_t n);

@@ -10,14 +10,15 @@
 
 namespace setrt {
 
-// Per-slot constants the last stage of every chain needs to publish the
-// output header (fixed when the slot is laid out; never rebound).
+// What the last stage of every chain needs to publish the output header (fixed
+// when the slot is laid out; outh is rebound where it points to host memory).
 struct SlotConst {
   DevSlotHdr* hdr;
   const uint64_t* tail;
-  set_out_header* outh;
+  set_out_header* outh;  // in the slot; in the job's host buffer where the kernel writes the output there
   uint64_t canary_head;
   uint64_t canary_tail;
+  uint64_t* word;        // completion word this kernel stores last, or null
 };
 
 // ---- argument blocks
@@ -25,6 +26,13 @@ struct BoxArgs {
   const uint8_t* in;
   uint16_t* S;
   int h, w;
+  DevSlotHdr* hdr;
+  JobScalars js;
+};
+struct BoxHistArgs {
+  const uint8_t* in;
+  int h, w;
+  uint32_t* partials;  // [grid][256]
   DevSlotHdr* hdr;
   JobScalars js;
 };
@@ -212,7 +220,9 @@ __global__ void k_hotspot_f32(HotspotArgs a);
 __global__ void k_box3_u8_u16(BoxArgs a);
 __global__ void k_div9_u16_u8(Div9Args a);
 __global__ void k_hist256_u8(HistArgs a);
+__global__ void k_box_hist_u8(BoxHistArgs a);
 __global__ void k_hist256_final(HistFinalArgs a);
+__global__ void k_copy_out_hist256(HistFinalArgs a);
 __global__ void k_gauss5_f32(GaussArgs a);
 template <int R, bool FULL>
 __global__ void k_gauss5_win_f32(GaussArgs a);
@@ -222,8 +232,10 @@ __global__ void k_sobel_thresh_f32(SobelArgs a);
 template <int R, bool FULL>
 __global__ void k_sobel_thresh_win_f32(SobelArgs a);
 __global__ void k_sobel_final(SobelFinalArgs a);
+__global__ void k_copy_out_sobel(SobelFinalArgs a);
 __global__ void k_saxpy_tanh_sum_f32(VecArgs a);
 __global__ void k_vec_final(VecFinalArgs a);
+__global__ void k_copy_out_vec(VecFinalArgs a);
 #if defined(__HIPCC__)
 // Sum over the wave in six DPP steps: two quad permutes, the half-row and row
 // mirrors (each lane then holds its 16-lane row's sum), then row_bcast:15 into

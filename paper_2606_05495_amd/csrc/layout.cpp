@@ -291,6 +291,12 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
   const uint64_t npix = (uint64_t)t.width * t.height;
   switch (t.pipeline) {
     case SET_PIPE_BOX_HIST_U8: {
+      if (!(t.flags & SET_TF_DEBUG)) {
+        const uint64_t bb = box_hist_blocks((int)t.height, (int)t.width);
+        stage("box_hist_u8", npix + bb * 1024);
+        stage("hist256_final", bb * 1024 + 1024 + 64);
+        break;
+      }
       const uint64_t hb = hist_blocks((int64_t)npix);
       stage("box3_u8_u16", npix + 2 * npix);
       stage("div9_u16_u8", 2 * npix + npix);

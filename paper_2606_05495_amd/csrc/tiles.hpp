@@ -80,6 +80,15 @@ inline unsigned div9_blocks(int64_t npix) {
 inline unsigned hist_blocks(int64_t npix) {
   return (unsigned)((npix + (int64_t)kBlock * kHistPerThread - 1) / ((int64_t)kBlock * kHistPerThread));
 }
+// Box sums, quotients and histogram in one kernel (templates without
+// intermediate images): 64 x 64 tiles, at most one block per partial row of the
+// slot's scratch, which hist_blocks sizes (ragged grids have more tiles).
+constexpr int kBoxHistTile = 64;
+inline unsigned box_hist_blocks(int h, int w) {
+  const uint64_t t = (uint64_t)((w + kBoxHistTile - 1) / kBoxHistTile) * ((h + kBoxHistTile - 1) / kBoxHistTile);
+  const unsigned hb = hist_blocks((int64_t)h * w);
+  return t < hb ? (unsigned)t : hb;
+}
 // Float images whose width is a multiple of 4 take the register-window
 // kernels: a lane owns 4 adjacent columns (16-byte loads and stores), a wave
 // 256 columns x R rows, a block 4 waves stacked vertically.  The Gaussian
