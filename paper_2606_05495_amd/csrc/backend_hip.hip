@@ -109,6 +109,7 @@ struct Pipe {
   void* placeholder = nullptr;  // pinned host buffer the memcpy nodes point at before the first bind
   uint64_t* words = nullptr;    // completion words, one 64-byte line per slot (SET_CB_HOST_FLAG)
   void* lib_ws = nullptr;       // library-call templates: temporary storage of every slot
+  bool direct = false;          // jobs are launched kernel by kernel (launches_directly)
   std::vector<Slot> slots;      // [w * d + s]
   std::vector<BatchGraph> batch;  // [count - 1]
 };
@@ -267,21 +268,24 @@ class HipBackend : public Backend {
         HIPCK(hipMemcpy(sl.base + p.L.tail, &ct, 8, hipMemcpyHostToDevice));
       }
     }
+    p.direct = launches_directly(p);
     if (cfg_.mode == SET_MODE_SET || cfg_.mode == SET_MODE_GRAPH || cfg_.mode == SET_MODE_QUEUE) {
       const int ds = (cfg_.mode == SET_MODE_SET) ? d_ : 1;
       for (int w = 0; w < b_; ++w) {
         for (int s = 0; s < ds; ++s) {
           Slot& sl = p.slots[(size_t)w * d_ + s];
-          int rc;
-          if ((t.flags & SET_TF_CAPTURE) || lib_template(t)) {
-            rc = capture_chain(p, sl, define_stream_, &sl.graph, &sl.nodes, err);
-          } else {
-            HIPCK(hipGraphCreate(&sl.graph, 0));
-            rc = add_chain(p, sl, sl.graph, &sl.nodes, err);
+          if (!p.direct) {
+            int rc;
+            if ((t.flags & SET_TF_CAPTURE) || lib_template(t)) {
+              rc = capture_chain(p, sl, define_stream_, &sl.graph, &sl.nodes, err);
+            } else {
+              HIPCK(hipGraphCreate(&sl.graph, 0));
+              rc = add_chain(p, sl, sl.graph, &sl.nodes, err);
+            }
+            if (rc != SET_OK) return rc;
+            HIPCK(hipGraphInstantiateWithFlags(&sl.exec, sl.graph, 0));
+            HIPCK(hipGraphUpload(sl.exec, define_stream_));
           }
-          if (rc != SET_OK) return rc;
-          HIPCK(hipGraphInstantiateWithFlags(&sl.exec, sl.graph, 0));
-          HIPCK(hipGraphUpload(sl.exec, define_stream_));
           if (cfg_.mode == SET_MODE_SET || cfg_.mode == SET_MODE_QUEUE)
             HIPCK(hipEventCreateWithFlags(&sl.ev, blocking_ ? (hipEventDisableTiming | hipEventBlockingSync)
                                                             : hipEventDisableTiming));
@@ -298,7 +302,7 @@ class HipBackend : public Backend {
     Pipe& p = *pipes_[j->tmpl];
     Slot& sl = p.slots[(size_t)j->worker * d_ + j->slot];
     set_scalars(p, sl, j);
-    const int rc = update_exec(p, sl, sl.exec, sl.nodes, err);
+    const int rc = p.direct ? SET_OK : update_exec(p, sl, sl.exec, sl.nodes, err);
     if (rc != SET_OK) return rc;
     // SET mode with input-copy streams: the input copy starts here, when the
     // job takes its FREE slot (nothing reads that slot's input any more), so
@@ -332,8 +336,12 @@ class HipBackend : public Backend {
     hipStream_t st = streams_[w];
     sl.cb = CbCtx{j, done, ctx};
     sl.flag_seq = j->seq;
-    HIPCK(input_ahead(p, sl, st, w));
-    HIPCK(hipGraphLaunch(sl.exec, st));
+    if (p.direct) {
+      HIPCK(enqueue_chain(p, sl, st, w));
+    } else {
+      HIPCK(input_ahead(p, sl, st, w));
+      HIPCK(hipGraphLaunch(sl.exec, st));
+    }
     switch (cfg_.callback_mode) {
       case SET_CB_EVENT_CHAIN: {
         HIPCK(hipEventRecord(sl.ev, st));
@@ -408,30 +416,7 @@ class HipBackend : public Backend {
     Slot& sl = p.slots[(size_t)si * d_];
     set_scalars(p, sl, j);
     hipStream_t st = streams_[si];
-    if (sl.in_bytes) {
-      if (in_by_kernel(p.t)) {
-        sl.h2d_copy = CopyArgs{sl.host_in, sl.base + p.L.in, sl.in_bytes};
-        HIPCK(hipLaunchKernel((const void*)&k_copy_in, dim3(kCopyBlocks), dim3(kBlock), sl.h2d_argv, 0, st));
-      } else if (in_ahead(p.t)) {
-        HIPCK(input_ahead(p, sl, st, si));
-      } else {
-        HIPCK(hipMemcpyAsync(sl.base + p.L.in, sl.host_in, sl.in_bytes, hipMemcpyHostToDevice, st));
-      }
-    }
-    if (delays(p)) HIPCK(launch_stress(p, sl, false, st));
-    for (int i = 0; i < sl.nstages; ++i) {
-      if (i == 1) HIPCK(library_stage(p, sl, st));
-      HIPCK(hipLaunchKernel(sl.func[i], sl.grid[i], dim3(sl.block[i]), sl.argv[i], 0, st));
-    }
-    if (writes_out(p.t)) {
-      // the last stage did
-    } else if (out_by_kernel(p.t)) {
-      sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
-      HIPCK(hipLaunchKernel((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), sl.d2h_argv, 0, st));
-    } else {
-      HIPCK(hipMemcpyAsync(sl.host_out, sl.base + p.L.out, sl.out_bytes, hipMemcpyDeviceToHost, st));
-    }
-    if (poisons(p)) HIPCK(launch_stress(p, sl, true, st));
+    HIPCK(enqueue_chain(p, sl, st, si));
     const uint64_t t0 = now_ns();
     HIPCK(hipStreamSynchronize(st));
     sync_ns_ += now_ns() - t0;
@@ -929,6 +914,23 @@ class HipBackend : public Backend {
     sl.delay = DelayArgs{us * clock_khz_ / 1000, 8 * us + 64};
   }
 
+  // Whether SET mode launches the template's jobs kernel by kernel instead of
+  // replaying a graph.  On ROCm a graph launch costs the dispatcher 14 us
+  // alone and 22-29 us beside others' whatever the graph holds, and a kernel
+  // launch 2-4 us, so a chain of up to six is the cheaper by itself, and needs
+  // no executable to update.  It pays where the host's launches set the pace;
+  // a job with more than 1 MiB to copy is longer on the link than in either
+  // (and its stages, launched apart, were held up behind other jobs' copies:
+  // four 1037 x 771 images with their intermediate images back, 524 us by
+  // graph, 595 us directly).  Small jobs, graph / direct: 64 of 256 x 256
+  // box/histogram 655 / 353 us, 256 uneven vector jobs 2060 / 925 us, 64
+  // thermal grids of 256^2 1095 / 890 us.  A captured template asks for graphs.
+  bool launches_directly(const Pipe& p) const {
+    if (cfg_.mode != SET_MODE_SET || (p.t.flags & SET_TF_CAPTURE) || lib_template(p.t) || !out_by_kernel(p.t))
+      return false;
+    const int copies = (p.L.in_cap > 0 ? 1 : 0) + (writes_out(p.t) ? 0 : 1);
+    return p.slots[0].nstages + copies <= 6 && p.L.in_cap + p.L.out_cap < (1ull << 20);
+  }
   // Point a last stage that writes the job's output itself at `out`.
   void set_out(Slot& sl, int pipeline, void* out) {
     char* o = static_cast<char*>(out);
@@ -1079,6 +1081,42 @@ class HipBackend : public Backend {
     hipError_t e = hipMemcpyAsync(sl.base + p.L.in, sl.host_in, sl.in_bytes, hipMemcpyHostToDevice, cs);
     if (e == hipSuccess) e = hipEventRecord(sl.in_ev, cs);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, sl.in_ev, 0);
+    return e;
+  }
+
+  // The bound job's chain, each piece enqueued by itself: the synchronous
+  // model, and the templates of SET mode that launch so (Pipe::direct).
+  hipError_t enqueue_chain(Pipe& p, Slot& sl, hipStream_t st, int w) {
+    auto run = [&](const void* f, dim3 grid, unsigned block, void** argv) {
+      return hipLaunchKernel(f, grid, dim3(block), argv, 0, st);
+    };
+    hipError_t e = hipSuccess;
+    if (sl.in_bytes) {
+      if (in_by_kernel(p.t)) {
+        sl.h2d_copy = CopyArgs{sl.host_in, sl.base + p.L.in, sl.in_bytes};
+        e = run((const void*)&k_copy_in, dim3(kCopyBlocks), kBlock, sl.h2d_argv);
+      } else if (in_ahead(p.t)) {
+        e = input_ahead(p, sl, st, w);
+      } else {
+        e = hipMemcpyAsync(sl.base + p.L.in, sl.host_in, sl.in_bytes, hipMemcpyHostToDevice, st);
+      }
+    }
+    if (e == hipSuccess && delays(p)) e = launch_stress(p, sl, false, st);
+    for (int i = 0; e == hipSuccess && i < sl.nstages; ++i) {
+      if (i == 1) e = library_stage(p, sl, st);
+      if (e == hipSuccess) e = run(sl.func[i], sl.grid[i], sl.block[i], sl.argv[i]);
+    }
+    if (e == hipSuccess && !writes_out(p.t)) {
+      if (out_by_kernel(p.t)) {
+        sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
+        e = run((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), kBlock, sl.d2h_argv);
+      } else {
+        e = hipMemcpyAsync(sl.host_out, sl.base + p.L.out, sl.out_bytes, hipMemcpyDeviceToHost, st);
+      }
+    }
+    if (e == hipSuccess && poisons(p)) e = launch_stress(p, sl, true, st);
+    if (e == hipSuccess && p.words && !flag_in_stage(p))
+      e = run((const void*)&k_done_flag, dim3(1), 64, sl.flag_argv);
     return e;
   }
 
