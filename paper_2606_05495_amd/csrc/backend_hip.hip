@@ -52,6 +52,7 @@ struct Slot {
   HistArgs hist;
   HistFinalArgs histf;
   GaussArgs gauss;
+  GaussSobelArgs gs;
   SobelArgs sobel;
   SobelFinalArgs sobelf;
   VecArgs vec;
@@ -811,6 +812,16 @@ class HipBackend : public Backend {
                              (float*)(b + L.scratch + q)};
         sl.sobelf = SobelFinalArgs{(const uint32_t*)(b + L.scratch), (const float*)(b + L.scratch + q), nb,
                                    (uint32_t*)payload, (float*)(payload + 4), sc};
+        if (one_kernel_image(t)) {
+          const Grid3 g = gauss_sobel_grid(h, w);
+          sl.gs = GaussSobelArgs{sl.gauss.in, h, w, taps[0], taps[1], taps[2], sl.sobel.thr, sl.sobel.pcount,
+                                 sl.sobel.psum, sc.hdr, JobScalars{}};
+          sl.sobelf.nparts = g.x * g.y;
+          stage(image_window_path(w) ? (const void*)&k_gauss_sobel_f32<true> : (const void*)&k_gauss_sobel_f32<false>,
+                to_dim3(g), &sl.gs, (unsigned)kGsBlock);
+          stage(wo ? (const void*)&k_copy_out_sobel : (const void*)&k_sobel_final, dim3(1), &sl.sobelf);
+          break;
+        }
         const bool win = image_window_path(w), full = window_full_width(w);
         const int gr = gauss_win_rows(h, w), sr = sobel_win_rows(h, w);
         // window kernels by rows per wave (2 or 4) and full-width variant
@@ -995,7 +1006,10 @@ class HipBackend : public Backend {
           sl.boxh.js = js;
         break;
       case SET_PIPE_GAUSS_SOBEL_F32:
-        sl.gauss.js = js;
+        if (one_kernel_image(p.t))
+          sl.gs.js = js;
+        else
+          sl.gauss.js = js;
         break;
       case SET_PIPE_SAXPY_TANH_SUM_F32:
         sl.vec.js = js;

@@ -563,6 +563,12 @@ template void k_sobel_thresh_win_f32<2, true>(SobelArgs);
 template void k_sobel_thresh_win_f32<2, false>(SobelArgs);
 template void k_sobel_thresh_win_f32<4, true>(SobelArgs);
 template void k_sobel_thresh_win_f32<4, false>(SobelArgs);
+template <bool COLUMNS_FIRST>
+void k_gauss_sobel_f32(GaussSobelArgs a) {
+  stamp(a.hdr, a.js);
+}
+template void k_gauss_sobel_f32<true>(GaussSobelArgs);
+template void k_gauss_sobel_f32<false>(GaussSobelArgs);
 void k_sobel_final(SobelFinalArgs a) { publish(a.sc); }
 void k_copy_out_sobel(SobelFinalArgs a) { publish(a.sc); }
 void k_saxpy_tanh_sum_f32(VecArgs a) { stamp(a.hdr, a.js); }
@@ -624,6 +630,8 @@ struct Register {
     register_kernel(&k_sobel_thresh_win_f32<2, false>);
     register_kernel(&k_sobel_thresh_win_f32<4, true>);
     register_kernel(&k_sobel_thresh_win_f32<4, false>);
+    register_kernel(&k_gauss_sobel_f32<true>);
+    register_kernel(&k_gauss_sobel_f32<false>);
     register_kernel(&k_sobel_final);
     register_kernel(&k_copy_out_sobel);
     register_kernel(&k_saxpy_tanh_sum_f32);

@@ -138,6 +138,11 @@ struct TemplateSizes {
   char stage_names[kMaxStages][32];
 };
 
+// Image templates that take the Gaussian and Sobel in one kernel.
+inline bool one_kernel_image(const set_job_template& t) {
+  return t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 && !(t.flags & SET_TF_DEBUG) &&
+         gauss_sobel_in_one((int)t.height, (int)t.width);
+}
 // Templates whose last stage, a kernel of one block, writes the job's output to
 // host memory itself: small outputs without intermediate images, of copy modes
 // whose output copy is a kernel.

@@ -76,6 +76,16 @@ struct SobelFinalArgs {
   float* out_sum;
   SlotConst sc;
 };
+struct GaussSobelArgs {
+  const float* in;
+  int h, w;
+  float g0, g1, g2;    // taps, as in GaussArgs
+  float thr;
+  uint32_t* pcount;    // [grid]
+  float* psum;         // [grid]
+  DevSlotHdr* hdr;
+  JobScalars js;
+};
 struct VecArgs {
   const float* x;      // pool base
   const float* y;
@@ -231,6 +241,8 @@ __global__ void k_gauss5_band_f32(GaussArgs a);
 __global__ void k_sobel_thresh_f32(SobelArgs a);
 template <int R, bool FULL>
 __global__ void k_sobel_thresh_win_f32(SobelArgs a);
+template <bool COLUMNS_FIRST>
+__global__ void k_gauss_sobel_f32(GaussSobelArgs a);
 __global__ void k_sobel_final(SobelFinalArgs a);
 __global__ void k_copy_out_sobel(SobelFinalArgs a);
 __global__ void k_saxpy_tanh_sum_f32(VecArgs a);

@@ -305,6 +305,13 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
       break;
     }
     case SET_PIPE_GAUSS_SOBEL_F32: {
+      if (one_kernel_image(t)) {
+        const Grid3 g = gauss_sobel_grid((int)t.height, (int)t.width);
+        const uint64_t nt = (uint64_t)g.x * g.y;
+        stage("gauss_sobel_f32", 4 * npix + 8 * nt);
+        stage("sobel_final", 8 * nt + 8 + 64);
+        break;
+      }
       const uint64_t nb = sobel_partials((int)t.height, (int)t.width);
       stage("gauss5_f32", 4 * npix + 4 * npix);
       stage("sobel_thresh_f32", 4 * npix + npix + 8 * nb);

@@ -134,6 +134,19 @@ inline uint64_t sobel_partials(int h, int w) {
   const Grid3 g = sobel_grid(h, w);
   return (uint64_t)g.x * g.y * (image_window_path(w) ? 4u : 1u);
 }
+// Gaussian and Sobel in one kernel (templates without intermediate images), 64
+// x 16 tiles of 512 threads: below 1024^2 pixels, and at any size for widths
+// that are not a multiple of 4, whose pair of kernels stages tiles in LDS as
+// well, twice.  Four jobs in the synchronous model, us, as a pair / in one:
+// 128^2 93 / 80, 333 x 250 117 / 103, 512^2 161 / 155, 1023 x 700 306 / 293,
+// 1501 x 1400 722 / 703; on the register windows 1024^2 390 / 384 and 2048^2
+// 1300 / 1309, so the line is drawn where the pair's second pass over memory
+// stops costing more than the one kernel's passes through LDS.
+constexpr int kGsBlock = 512;
+inline bool gauss_sobel_in_one(int h, int w) { return !image_window_path(w) || (int64_t)h * w < (int64_t)1024 * 1024; }
+inline Grid3 gauss_sobel_grid(int h, int w) {
+  return {(unsigned)((w + kSobelTW - 1) / kSobelTW), (unsigned)((h + kSobelTH - 1) / kSobelTH), 1u};
+}
 // Thermal-grid step: the register window (4 columns x kHotWinRows rows per
 // lane) for widths that are multiples of 4, one pixel per thread otherwise.
 constexpr int kHotWinRows = 2;
