@@ -521,7 +521,7 @@ int set_run_vector_jobs(set_ctx *c, int template_id, const set_vec_job *jobs, ui
  *
  * device: HIP device ordinal; made current for the call, then restored.
  * stream: hipStream_t of that device (NULL = its null stream).  The call only
- *   enqueues three kernels there and returns; results are ready when the
+ *   enqueues two or three kernels there and returns; results are ready when the
  *   stream's work before the next synchronisation point has finished.
  * dev_x_pool, dev_y_pool: device float pools of pool_len elements each.
  * dev_jobs: device array of count set_vec_job; dev_results: device float

@@ -1400,27 +1400,20 @@ __device__ inline uint32_t vec_find_job(const VecBatchDesc* D, uint32_t count, u
   return lo;
 }
 
-// A batch's tiles are claimed in runs of H->claim.  Block b starts with run b;
-// further runs come from the batch's counter, asked for before the loads of a
-// run's last tile and answered behind them.  Wave 0 finds the next tile's job
-// and leaves its descriptor in LDS; one barrier ends a tile (the LDS words are
-// double, so the next tile's writes cannot meet this one's reads).  A tile's
-// partial depends on its job and BLOCK only, so which block takes it changes no
-// result.
-// Bound by memory from about 100 MB a call: 7.1 TB/s over jobs of 2^20 and more
-// at every block size (256 threads: 6.7 before, with one pair of loads in
-// flight and the atomic and a binary search ahead of each unit); 64 uneven jobs,
-// 310 MB, 256 threads, on the no-allocation call: 181 us before, 70 us now.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
+// A block's tiles: `first`, then what next(t) names after tile t, up to T (both
+// the same in every thread; only thread 0's next counts).  next is asked before
+// a tile's loads, so that a claim is answered behind them.  Wave 0 finds the
+// next tile's job and leaves its descriptor in LDS; one barrier ends a tile (the
+// LDS words are double, so the next tile's writes cannot meet this one's
+// reads).  A tile's partial depends on its job and BLOCK only, so which block
+// takes it changes no result.
+template <int BLOCK, class Next>
+__device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count, uint32_t T, uint32_t first,
+                                          const float* px, const float* py, float* partials, Next next) {
   constexpr int W = BLOCK / 64;
   __shared__ float s_sum[2][kVecUnitsPerItem][W];
   __shared__ uint32_t s_tile[2];
   __shared__ VecBatchDesc s_desc[2];
-  if (blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
-  const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
-  const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
-  const uint32_t count = H->count, T = H->total_tiles, run = H->claim;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   constexpr int kDescWords = sizeof(VecBatchDesc) / 4;
@@ -1432,25 +1425,13 @@ __global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
     }
     if (lane == 0) s_tile[slot] = t;
   };
-  const uint64_t first = (uint64_t)blockIdx.x * run, dealt = (uint64_t)gridDim.x * run;
-  if (first >= T) return;
   int cur = 0;
-  uint32_t left = run;  // tiles of the run still to do, the current one included
-  if (wave == 0) publish((uint32_t)first, 0);
+  if (wave == 0) publish(first, 0);
   __syncthreads();
   while (true) {
     const uint32_t t = __builtin_amdgcn_readfirstlane(s_tile[cur]);
     if (t >= T) break;
-    uint32_t next = t + 1;
-    if (--left == 0) {
-      left = run;
-      next = T;
-      if (T > dealt && threadIdx.x == 0) {
-        const uint64_t u =
-            dealt + (uint64_t)run * __hip_atomic_fetch_add(a.work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        next = u < T ? (uint32_t)u : T;
-      }
-    }
+    const uint32_t after = next(t);
     const VecBatchDesc& d = s_desc[cur];
     auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
     auto scalar64 = [&](uint64_t v) { return (uint64_t)scalar((uint32_t)(v >> 32)) << 32 | scalar((uint32_t)v); };
@@ -1458,27 +1439,96 @@ __global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
     const uint64_t beg = (uint64_t)(t - scalar(d.tile_start)) * te;
     const uint64_t len = beg + te < n ? te : n - beg;
     const float av = __int_as_float((int)scalar((uint32_t)__float_as_int(d.a)));
-    const float* x = a.x + scalar64(d.x_off) + beg;
-    const float* y = a.y + scalar64(d.y_off) + beg;
+    const float* x = px + scalar64(d.x_off) + beg;
+    const float* y = py + scalar64(d.y_off) + beg;
     int units = 0;
     for (uint64_t u = 0; u < len; u += ue, ++units) {
       const float ws = wave_total_f32(vec_range_sum<BLOCK>(x + u, y + u, av, len - u < ue ? len - u : ue));
       if (lane == 0) s_sum[cur][units][wave] = ws;
     }
-    if (wave == 0) publish(__builtin_amdgcn_readfirstlane(next), cur ^ 1);
+    if (wave == 0) publish(scalar(after), cur ^ 1);
     __syncthreads();
     if (threadIdx.x == 0) {
       float s = tree_sum_f32<W>(s_sum[cur][0]);
       for (int u = 1; u < units; ++u) s += tree_sum_f32<W>(s_sum[cur][u]);
-      a.partials[t] = s;
+      partials[t] = s;
     }
     cur ^= 1;
   }
+}
+
+// A batch's tiles are claimed in runs of H->claim.  Block b starts with run b;
+// further runs come from the batch's counter.
+// Bound by memory from about 100 MB a call: 7.1 TB/s over jobs of 2^20 and more
+// at every block size (256 threads: 6.7 before, with one pair of loads in
+// flight and the atomic and a binary search ahead of each unit).
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
+  const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
+  const uint32_t T = H->total_tiles, run = H->claim;
+  const uint64_t first = (uint64_t)blockIdx.x * run, dealt = (uint64_t)gridDim.x * run;
+  if (first >= T) return;
+  uint32_t left = run;  // tiles of the run still to do, the current one included
+  vec_tiles<BLOCK>(D, H->count, T, (uint32_t)first, a.x, a.y, a.partials, [&](uint32_t t) {
+    if (--left != 0) return t + 1;
+    left = run;
+    uint32_t after = T;
+    if (T > dealt && threadIdx.x == 0) {
+      const uint64_t u =
+          dealt + (uint64_t)run * __hip_atomic_fetch_add(a.work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      after = u < T ? (uint32_t)u : T;
+    }
+    return after;
+  });
 }
 template __global__ void k_vec_batch_tiles<128>(VecBatchArgs);
 template __global__ void k_vec_batch_tiles<256>(VecBatchArgs);
 template __global__ void k_vec_batch_tiles<512>(VecBatchArgs);
 template __global__ void k_vec_batch_tiles<1024>(VecBatchArgs);
+
+// The tile kernel of a no-allocation call of at most kBlock jobs: every block
+// plans the call for itself, a job a thread, in LDS, and block 0 leaves the
+// table for the totals.  Tiles are dealt in turn, without a counter.  Without
+// the planning kernel and the claims a small call takes 12-14 us instead of 17,
+// and 64 uneven jobs (310 MB) 56 us instead of 70 (181 before the loads of
+// vec_range_sum went out together).
+__global__ __launch_bounds__(kBlock, 8) void k_vec_few_tiles(VecFewArgs a) {
+  __shared__ VecBatchDesc s_table[kBlock];
+  __shared__ uint32_t s_wave[kBlock / 64];
+  const uint32_t j = threadIdx.x, lane = j & 63u, wave = j >> 6;
+  VecBatchDesc d{};
+  if (j < a.plan.count) d = vec_plan_job(a.plan, a.plan.jobs[j]);
+  uint32_t upto = d.ntiles;  // inclusive prefix within the wave, then over the waves
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t u = __shfl_up(upto, off, 64);
+    if (lane >= (uint32_t)off) upto += u;
+  }
+  if (lane == 63) s_wave[wave] = upto;
+  __syncthreads();
+  uint32_t before = 0, T = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kBlock / 64; ++k) {
+    if (k < wave) before += s_wave[k];
+    T += s_wave[k];
+  }
+  d.tile_start = before + upto - d.ntiles;
+  s_table[j] = d;
+  if (blockIdx.x == 0) {
+    VecBatchHdr* H = reinterpret_cast<VecBatchHdr*>(a.plan.tab);
+    if (j < a.plan.count) reinterpret_cast<VecBatchDesc*>(a.plan.tab + sizeof(VecBatchHdr))[j] = d;
+    if (j == 0) {
+      H->count = a.plan.count;
+      H->total_tiles = T;
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x >= T) return;
+  vec_tiles<kBlock>(s_table, a.plan.count, T, blockIdx.x, a.x, a.y, a.partials,
+                    [&](uint32_t t) { return gridDim.x < T - t ? t + gridDim.x : T; });
+}
 
 // Job j = wave: its tiles' partials in a fixed order.  Block 0 also rewinds the
 // work counter for the slot's next batch and publishes the header.

@@ -107,6 +107,25 @@ struct VecBatchArgs {
   DevSlotHdr* hdr;
   JobScalars js;
 };
+// Planning of a no-allocation call: jobs to descriptors.
+struct VecPlanArgs {
+  const set_vec_job* jobs;
+  uint32_t count;
+  uint32_t grid;            // blocks of the tile kernel
+  uint64_t max_n;
+  uint64_t pool_len;
+  uint8_t* tab;             // VecBatchHdr + VecBatchDesc[count]
+  uint32_t* work;           // claim counter
+  uint32_t split;           // a tile is a unit of a work item, not all of it
+  uint32_t item_elems[64];  // elements per work item, per size bucket
+};
+struct VecFewArgs {
+  VecPlanArgs plan;
+  const float* x;
+  const float* y;
+  float* partials;
+};
+__global__ void k_vec_few_tiles(VecFewArgs a);
 struct VecBatchFinalArgs {
   const uint8_t* tab;
   const float* partials;
@@ -266,6 +285,20 @@ __device__ inline float wave_total_f32(float v) {
   v += __int_as_float(dpp_i<0x142, 0xa>(__float_as_int(v)));  // row_bcast:15
   v += __int_as_float(dpp_i<0x143, 0xc>(__float_as_int(v)));  // row_bcast:31
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+// Descriptor of a no-allocation call's job, but for its first tile; all zero for
+// a job that is rejected.
+__device__ inline VecBatchDesc vec_plan_job(const VecPlanArgs& a, const set_vec_job& v) {
+  VecBatchDesc d{};
+  const bool ok = v.n >= 1 && v.n <= a.max_n && v.x_off <= a.pool_len && v.n <= a.pool_len - v.x_off &&
+                  v.y_off <= a.pool_len && v.n <= a.pool_len - v.y_off;
+  if (ok) {
+    d.x_off = v.x_off;
+    d.y_off = v.y_off;
+    d.a = v.a;
+    vec_set_tiles(d, (uint32_t)v.n, a.item_elems[63 - __builtin_clzll(v.n)], kBlock, a.split != 0);
+  }
+  return d;
 }
 // Sum of one vector job's tile partials by one wave: a work item's tiles in
 // order, lane l the items l, l + 64, ..., then the lanes' sums.  Items whose

@@ -9,7 +9,8 @@
 // work counter live in one static device array per GPU, whose address is
 // looked up once per device.
 //
-// Three launches on the caller's stream:
+// Up to kBlock jobs take two launches on the caller's stream, a tile kernel whose
+// blocks each plan the call in LDS and the totals; more take three:
 //   plan   (one block): validate each job, pick its item size, prefix-sum the
 //          tile counts into a descriptor table and rewind the work counter;
 //   tiles  (persistent grid): the batch pipeline's (job, tile) kernel;
@@ -52,18 +53,6 @@ static __device__ __align__(256) unsigned char scratch[setrt::kNaBytes];
 namespace setrt {
 namespace {
 
-struct NaPlanArgs {
-  const set_vec_job* jobs;
-  uint32_t count;
-  uint32_t grid;       // blocks of the tile kernel
-  uint64_t max_n;
-  uint64_t pool_len;
-  uint8_t* tab;
-  uint32_t* work;
-  uint32_t split;           // a tile is a unit of a work item, not all of it
-  uint32_t item_elems[64];  // elements per work item, per size bucket
-};
-
 struct NaTotalsArgs {
   const uint8_t* tab;
   const float* partials;
@@ -93,7 +82,7 @@ __device__ inline uint32_t block_excl_u32(uint32_t v, uint32_t* s_wave, uint32_t
   return before + incl - v;
 }
 
-__global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(NaPlanArgs a) {
+__global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(VecPlanArgs a) {
   __shared__ uint32_t s_wave[kNaPlanThreads / 64];
   __shared__ unsigned long long s_elems;
   VecBatchDesc* D = reinterpret_cast<VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
@@ -103,17 +92,7 @@ __global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(NaPlanArgs 
   for (uint32_t base = 0; base < a.count; base += kNaPlanThreads) {
     const uint32_t j = base + threadIdx.x;
     VecBatchDesc d{};
-    if (j < a.count) {
-      const set_vec_job v = a.jobs[j];
-      const bool ok = v.n >= 1 && v.n <= a.max_n && v.x_off <= a.pool_len && v.n <= a.pool_len - v.x_off &&
-                      v.y_off <= a.pool_len && v.n <= a.pool_len - v.y_off;
-      if (ok) {
-        d.x_off = v.x_off;
-        d.y_off = v.y_off;
-        d.a = v.a;
-        vec_set_tiles(d, (uint32_t)v.n, a.item_elems[63 - __builtin_clzll(v.n)], kBlock, a.split != 0);
-      }
-    }
+    if (j < a.count) d = vec_plan_job(a, a.jobs[j]);
     uint32_t chunk_total;
     const uint32_t excl = block_excl_u32(d.ntiles, s_wave, &chunk_total);
     d.tile_start = carry + excl;
@@ -181,7 +160,7 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     return na_fail(SET_EINVAL, "count " + std::to_string(count) + " above the maximum of " +
                                    std::to_string(kNaMaxJobs) + " jobs per call");
   if (grid > 65535) return na_fail(SET_EINVAL, "grid above 65535");
-  NaPlanArgs pa{};
+  VecPlanArgs pa{};
   // Item size per bucket and the most items any job of length <= max_n needs.
   const int top = 63 - __builtin_clzll(max_n);
   uint64_t worst = 0, worst_units = 0;
@@ -219,10 +198,15 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     pa.work = work;
     pa.split = count * worst_units <= kNaMaxItems;
     pa.grid = grid ? grid : (uint32_t)kVecBatchGrid;
-    hipLaunchKernelGGL(k_vec_noalloc_plan, dim3(1), dim3(kNaPlanThreads), 0, stream, pa);
-    JobScalars js{};
-    VecBatchArgs va{tab, x, y, partials, work, reinterpret_cast<DevSlotHdr*>(base + kNaHdrOff), js};
-    hipLaunchKernelGGL(k_vec_batch_tiles<kBlock>, dim3(pa.grid), dim3(kBlock), 0, stream, va);
+    if (count <= (uint64_t)kBlock) {
+      VecFewArgs fa{pa, x, y, partials};
+      hipLaunchKernelGGL(k_vec_few_tiles, dim3(pa.grid), dim3(kBlock), 0, stream, fa);
+    } else {
+      hipLaunchKernelGGL(k_vec_noalloc_plan, dim3(1), dim3(kNaPlanThreads), 0, stream, pa);
+      JobScalars js{};
+      VecBatchArgs va{tab, x, y, partials, work, reinterpret_cast<DevSlotHdr*>(base + kNaHdrOff), js};
+      hipLaunchKernelGGL(k_vec_batch_tiles<kBlock>, dim3(pa.grid), dim3(kBlock), 0, stream, va);
+    }
     NaTotalsArgs ta{tab, partials, results};
     hipLaunchKernelGGL(k_vec_noalloc_totals, dim3((unsigned)((count + kVecFinalJobs - 1) / kVecFinalJobs)), dim3(kBlock),
                        0, stream, ta);

@@ -98,11 +98,12 @@ def test_lengths_around_rows_and_units(torch_gpu, pools, block):
         assert abs(float(res[i]) - S) <= oracle.vec_tolerance(S, E), (block, int(j["n"]), res[i], S)
 
 
-@pytest.mark.parametrize("count,n_max,grid", [(1, 5, 0), (64, 70000, 0), (65, 300, 3), (257, 20000, 1), (4097, 3000, 0),
+@pytest.mark.parametrize("count,n_max,grid", [(1, 5, 0), (64, 70000, 0), (65, 300, 3), (256, 9000, 2), (257, 20000, 1), (4097, 3000, 0),
                                               (16384, 1500, 5)])
 def test_job_search_and_claims(torch_gpu, pools, count, n_max, grid):
     """Tables of one to three rounds of the job search, rejected jobs among
-    them, on few blocks (many claims, runs of several units) and on many."""
+    them, on few blocks (many claims, runs of several units) and on many; up to 256
+    jobs each block plans for itself."""
     print("job search", count, n_max, grid)
     sys.stdout.flush()
     x, y, xd, yd = pools
