@@ -786,8 +786,9 @@ class HipBackend : public Backend {
           const unsigned bb = box_hist_blocks(h, w);
           sl.boxh = BoxHistArgs{(const uint8_t*)(b + L.in), h, w, (uint32_t*)(b + L.scratch), sc.hdr, JobScalars{}};
           sl.histf = HistFinalArgs{(const uint32_t*)(b + L.scratch), bb, (uint32_t*)payload, sc};
-          stage((const void*)&k_box_hist_u8, dim3(bb), &sl.boxh);
-          stage(wo ? (const void*)&k_copy_out_hist256 : (const void*)&k_hist256_final, dim3(1), &sl.histf);
+          stage((const void*)&k_box_hist_u8, dim3(bb), &sl.boxh, (unsigned)kBoxHistBlock);
+          stage(wo ? (const void*)&k_copy_out_hist256 : (const void*)&k_hist256_final, dim3(1), &sl.histf,
+                (unsigned)kHistFinalBlock);
           break;
         }
         const unsigned hb = hist_blocks(npix);
@@ -798,7 +799,7 @@ class HipBackend : public Backend {
         stage((const void*)&k_box3_u8_u16, to_dim3(box_grid(h, w)), &sl.box);
         stage((const void*)&k_div9_u16_u8, dim3(div9_blocks(npix)), &sl.div);
         stage((const void*)&k_hist256_u8, dim3(hb), &sl.hist);
-        stage((const void*)&k_hist256_final, dim3(1), &sl.histf);
+        stage((const void*)&k_hist256_final, dim3(1), &sl.histf, (unsigned)kHistFinalBlock);
         break;
       }
       case SET_PIPE_GAUSS_SOBEL_F32: {

@@ -242,75 +242,52 @@ __global__ __launch_bounds__(kBlock) void k_job_end(JobEndArgs a) {
 
 // ------------------------------------------------------------------ box sum, floor(s / 9) and histogram in one
 // For templates that return the histogram alone: the sums and quotients stay in
-// registers.  A thread takes 16 pixels of a row, four threads a row of the
-// block's 64 x 64 tile; its three input rows come as 16-byte loads at any
-// alignment (a byte either side for the neighbours) and are added column-wise
-// two to a word.  Quotients go to per-wave LDS bins.  The grid is at most the
-// partial rows the slot has, so a block may take several tiles.
-// Small images are launch and memory latency: as three kernels a 256^2 image took
-// 3.3 + 2.2 + 2.5 us and two launches.  64 jobs of 256^2, this and the output
-// written by the last kernel: 697 -> 650 us.
-typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(1)));
-__global__ __launch_bounds__(kBlock) void k_box_hist_u8(BoxHistArgs a) {
+// registers.  A thread takes 4 pixels of a row, 16 threads a row of the block's
+// 64 x 64 tile.  Of each of its three input rows it loads the 8 bytes from one
+// left of its pixels, at any alignment (before the first and past the last row
+// of the image they reach into the slot around it, and are masked), and adds
+// them column-wise two to a word.  Quotients go to LDS bins, four copies.  The
+// grid is at most the partial rows the slot has, so a block may take several
+// tiles.
+// Small images are launch and memory latency, of the code too: a kernel this
+// short runs once over its instructions, cold (16 pixels a thread, unrolled with
+// a byte path for ragged ends, 4.4 KB of code: 3.3 us for 256^2 and 6.5 for 333
+// x 250; now 2.8 and 3.3; as three kernels 2.5 + 2.1 + 2.2).
+typedef uint32_t v2u_any __attribute__((ext_vector_type(2), aligned(1)));
+__global__ __launch_bounds__(kBoxHistBlock) void k_box_hist_u8(BoxHistArgs a) {
   __shared__ uint32_t wh[4][256];
-  const int tid = threadIdx.x, wave = tid >> 6;
+  const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid == 0) write_slot_hdr(a.hdr, a.js);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) wh[k][tid] = 0u;
+  (&wh[0][0])[tid] = 0u;
   __syncthreads();
+  uint32_t* bins = wh[(tid >> 6) & 3];
   const int tiles_x = (a.w + kBoxHistTile - 1) / kBoxHistTile, tiles_y = (a.h + kBoxHistTile - 1) / kBoxHistTile;
-  const int tiles = tiles_x * tiles_y;
-  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+  for (int t = blockIdx.x; t < tiles_x * tiles_y; t += gridDim.x) {
     const int by = t / tiles_x, bx = t - by * tiles_x;
-    const int x = bx * kBoxHistTile + 16 * (tid & 3), y = by * kBoxHistTile + (tid >> 2);
+    const int x = bx * kBoxHistTile + 4 * (tid & 15), y = by * kBoxHistTile + (tid >> 4);
     if (x >= a.w || y >= a.h) continue;
-    uint32_t even[4] = {0u, 0u, 0u, 0u}, odd[4] = {0u, 0u, 0u, 0u}, left = 0u, right = 0u;
-    v4u_any v[3];
-    uint32_t l[3], r[3];
+    uint32_t even0 = 0, odd0 = 0, even1 = 0, odd1 = 0;  // columns x-1, x+1 | x, x+2 | x+3 | x+4
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int yr = y + k - 1;
-      v[k] = v4u_any{0u, 0u, 0u, 0u};
-      l[k] = r[k] = 0u;
-      if (yr >= 0 && yr < a.h) {
-        const uint8_t* row = a.in + (size_t)yr * a.w;
-        if (x > 0) l[k] = row[x - 1];
-        if (x + 16 < a.w) r[k] = row[x + 16];
-        if (x + 16 <= a.w) {
-          v[k] = *reinterpret_cast<const v4u_any*>(row + x);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (x + i < a.w) v[k][i >> 2] |= (uint32_t)row[x + i] << (8 * (i & 3));
-        }
-      }
+    for (int k = -1; k <= 1; ++k) {
+      const int yr = y + k;
+      const v2u_any v = *reinterpret_cast<const v2u_any*>(a.in + (ptrdiff_t)clampi(yr, 0, a.h - 1) * a.w + x - 1);
+      const uint32_t keep = yr >= 0 && yr < a.h ? 0x00FF00FFu : 0u;
+      even0 += v.x & keep;
+      odd0 += (v.x >> 8) & keep;
+      even1 += v.y & keep;
+      odd1 += (v.y >> 8) & keep;
     }
+    uint32_t c[6] = {even0 & 0xFFFFu, odd0 & 0xFFFFu, even0 >> 16, odd0 >> 16, even1 & 0xFFFFu, odd1 & 0xFFFFu};
+    if (x == 0) c[0] = 0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      left += l[k];
-      right += r[k];
+    for (int i = 2; i < 6; ++i)
+      if (x + i - 1 >= a.w) c[i] = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        even[i] += v[k][i] & 0x00FF00FFu;
-        odd[i] += (v[k][i] >> 8) & 0x00FF00FFu;
-      }
-    }
-    uint32_t c[18];
-    c[0] = left;
-    c[17] = right;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      c[4 * i + 1] = even[i] & 0xFFFFu;
-      c[4 * i + 2] = odd[i] & 0xFFFFu;
-      c[4 * i + 3] = even[i] >> 16;
-      c[4 * i + 4] = odd[i] >> 16;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (x + i < a.w) atomicAdd(&wh[wave][(c[i] + c[i + 1] + c[i + 2]) / 9u], 1u);
+    for (int i = 0; i < 4; ++i)
+      if (x + i < a.w) atomicAdd(&bins[(c[i] + c[i + 1] + c[i + 2]) / 9u], 1u);
   }
   __syncthreads();
-  a.partials[(size_t)blockIdx.x * 256 + tid] = wh[0][tid] + wh[1][tid] + wh[2][tid] + wh[3][tid];
+  if (tid < 256) a.partials[(size_t)blockIdx.x * 256 + tid] = wh[0][tid] + wh[1][tid] + wh[2][tid] + wh[3][tid];
 }
 
 // ------------------------------------------------------------------ 3x3 box sum (zero padded), uint8 -> uint16
@@ -384,35 +361,38 @@ __global__ __launch_bounds__(kBlock) void k_hist256_u8(HistArgs a) {
 }
 
 // One block: bin tid = sum of the blocks' partial counts (integer, exact in
-// any order).  The loads go out 16 blocks at a time with no branch between
-// them (past the last block the index is clamped and the value dropped), so
-// one memory latency covers 16 blocks instead of one.
+// any order).  Four quarters of the block take every fourth row, 16 loads of
+// each going out at a time with no branch between them (past the last row the
+// index is clamped and the value dropped): one memory latency covers 64 rows.
 // Like the other combining kernels it has two names: k_copy_out_* where it
 // writes the job's output to host memory itself (it is then the job's output
 // copy, and its completion where the template completes by words, which saves
 // a launch or two of about 2 us each), k_*_final where a copy follows.
 __device__ __forceinline__ void hist256_final(const HistFinalArgs& a) {
-  const int tid = threadIdx.x;
+  __shared__ uint32_t part[4][256];
+  const int tid = threadIdx.x & 255, quarter = threadIdx.x >> 8;
   const unsigned nb = a.nblocks;
   OutWords w{};
-  if (tid == 0) w = load_out(a.sc);
+  if (threadIdx.x == 0) w = load_out(a.sc);
   uint32_t s = 0;
-  for (unsigned b0 = 0; b0 < nb; b0 += 16) {
+  for (unsigned b0 = quarter; b0 < nb; b0 += 64) {  // rows b0, b0 + 4, ..., b0 + 60
     uint32_t v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-      const unsigned b = b0 + k < nb ? b0 + k : nb - 1;
+      const unsigned b = b0 + 4 * k < nb ? b0 + 4 * k : nb - 1;
       v[k] = a.partials[(size_t)b * 256 + tid];
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) s += b0 + k < nb ? v[k] : 0u;
+    for (int k = 0; k < 16; ++k) s += b0 + 4 * k < nb ? v[k] : 0u;
   }
-  a.H[tid] = s;
-  if (tid == 0) store_out(a.sc, w, true);
+  part[quarter][tid] = s;
+  __syncthreads();
+  if (threadIdx.x < 256) a.H[tid] = part[0][tid] + part[1][tid] + part[2][tid] + part[3][tid];
+  if (threadIdx.x == 0) store_out(a.sc, w, true);
   complete_out(a.sc, w.h.seq);
 }
-__global__ __launch_bounds__(kBlock) void k_hist256_final(HistFinalArgs a) { hist256_final(a); }
-__global__ __launch_bounds__(kBlock) void k_copy_out_hist256(HistFinalArgs a) { hist256_final(a); }
+__global__ __launch_bounds__(kHistFinalBlock) void k_hist256_final(HistFinalArgs a) { hist256_final(a); }
+__global__ __launch_bounds__(kHistFinalBlock) void k_copy_out_hist256(HistFinalArgs a) { hist256_final(a); }
 
 // ------------------------------------------------------------------ separable 5-tap Gaussian, replicated borders
 // Input tile (kGaussTH+4) x (kGaussTW+4) in LDS, horizontal pass into a

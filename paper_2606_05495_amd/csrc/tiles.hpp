@@ -81,13 +81,18 @@ inline unsigned hist_blocks(int64_t npix) {
   return (unsigned)((npix + (int64_t)kBlock * kHistPerThread - 1) / ((int64_t)kBlock * kHistPerThread));
 }
 // Box sums, quotients and histogram in one kernel (templates without
-// intermediate images): 64 x 64 tiles, at most one block per partial row of the
-// slot's scratch, which hist_blocks sizes (ragged grids have more tiles).
+// intermediate images): 64 x 64 tiles, at most a block for each compute unit
+// (one block combines the partial rows: of 2048^2 pixels 1024 rows took it 34
+// us, 256 take it 4.6) and for each partial row of the slot's scratch, which
+// hist_blocks sizes (ragged grids have more tiles).
 constexpr int kBoxHistTile = 64;
+constexpr int kBoxHistBlock = 1024;
+constexpr int kHistFinalBlock = 1024;
 inline unsigned box_hist_blocks(int h, int w) {
   const uint64_t t = (uint64_t)((w + kBoxHistTile - 1) / kBoxHistTile) * ((h + kBoxHistTile - 1) / kBoxHistTile);
   const unsigned hb = hist_blocks((int64_t)h * w);
-  return t < hb ? (unsigned)t : hb;
+  const uint64_t b = t < hb ? t : hb;
+  return (unsigned)(b < 256 ? b : 256);
 }
 // Float images whose width is a multiple of 4 take the register-window
 // kernels: a lane owns 4 adjacent columns (16-byte loads and stores), a wave
