@@ -62,7 +62,8 @@ struct Slot {
   ScanDownArgs scan_d;
   VecBatchArgs vb;
   VecBatchFinalArgs vbf;
-  CopyArgs h2d_copy, d2h_copy;
+  CopyArgs h2d_copy;
+  CopyOutArgs d2h_copy;
   void* h2d_argv[1] = {&h2d_copy};
   void* d2h_argv[1] = {&d2h_copy};
   DoneFlagArgs flag{};
@@ -133,6 +134,12 @@ inline dim3 to_dim3(Grid3 g) { return dim3(g.x, g.y, g.z); }
 inline bool in_by_kernel(const set_job_template& t) { return t.copy_mode == SET_COPY_KERNELS; }
 inline bool in_ahead(const set_job_template& t) { return t.copy_mode == SET_COPY_ASYNC_IN; }
 inline bool out_by_kernel(const set_job_template& t) { return t.copy_mode != SET_COPY_NODES; }
+
+// The output copy kernel of a template, and its argument block CopyOutArgs
+// (k_copy_out takes the CopyArgs at its start).
+inline const void* out_copy(const set_job_template& t) {
+  return publishes_in_copy(t) ? (const void*)&k_copy_out_publish : (const void*)&k_copy_out;
+}
 
 // Templates whose middle stage is a library call captured into the job
 // graph (between stage kernel 0 and stage kernel 1).
@@ -566,9 +573,9 @@ class HipBackend : public Backend {
       if (copy_out) {
         if (writes_out(p.t)) return hipSuccess;  // part of the last stage
         if (out_by_kernel(p.t)) {
-          CopyArgs ca{sl.base + p.L.out, p.placeholder, out_b};
+          CopyOutArgs ca{CopyArgs{sl.base + p.L.out, p.placeholder, out_b}, sl.d2h_copy.sc};
           void* av[1] = {&ca};
-          return hipLaunchKernel((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), av, 0, st);
+          return hipLaunchKernel(out_copy(p.t), dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), av, 0, st);
         }
         return hipMemcpyAsync(p.placeholder, sl.base + p.L.out, out_b, hipMemcpyDeviceToHost, st);
       }
@@ -780,6 +787,7 @@ class HipBackend : public Backend {
       ++sl.nstages;
     };
     sl.nstages = 0;
+    sl.d2h_copy.sc = sc;
     switch (t.pipeline) {
       case SET_PIPE_BOX_HIST_U8: {
         if (!(t.flags & SET_TF_DEBUG)) {
@@ -890,8 +898,10 @@ class HipBackend : public Backend {
           else
             stage(hk, to_dim3(hotspot_grid(h, w)), &sl.hot[k]);
         }
-        sl.je = JobEndArgs{sc};
-        stage((const void*)&k_job_end, dim3(1), &sl.je);
+        if (!publishes_in_copy(t)) {
+          sl.je = JobEndArgs{sc};
+          stage((const void*)&k_job_end, dim3(1), &sl.je);
+        }
         break;
       }
       case SET_PIPE_SCAN_LIB_I32_I64:
@@ -1052,9 +1062,9 @@ class HipBackend : public Backend {
     return kp;
   }
 
-  hipKernelNodeParams copy_params(void** argv, bool to_device, unsigned blocks = kCopyBlocks) {
+  hipKernelNodeParams copy_params(const Pipe& p, void** argv, bool to_device, unsigned blocks = kCopyBlocks) {
     hipKernelNodeParams kp{};
-    kp.func = to_device ? (void*)&k_copy_in : (void*)&k_copy_out;
+    kp.func = to_device ? (void*)&k_copy_in : const_cast<void*>(out_copy(p.t));
     kp.gridDim = dim3(blocks);
     kp.blockDim = dim3(kBlock);
     kp.sharedMemBytes = 0;
@@ -1123,8 +1133,8 @@ class HipBackend : public Backend {
     }
     if (e == hipSuccess && !writes_out(p.t)) {
       if (out_by_kernel(p.t)) {
-        sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
-        e = run((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), kBlock, sl.d2h_argv);
+        sl.d2h_copy.c = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
+        e = run(out_copy(p.t), dim3(d2h_copy_blocks(p.L.out_cap)), kBlock, sl.d2h_argv);
       } else {
         e = hipMemcpyAsync(sl.host_out, sl.base + p.L.out, sl.out_bytes, hipMemcpyDeviceToHost, st);
       }
@@ -1145,7 +1155,7 @@ class HipBackend : public Backend {
     if (p.L.in_cap > 0 && !in_ahead(p.t)) {
       if (kcopy) {
         sl.h2d_copy = CopyArgs{p.placeholder, sl.base + p.L.in, p.L.in_cap};
-        hipKernelNodeParams kp = copy_params(sl.h2d_argv, true);
+        hipKernelNodeParams kp = copy_params(p, sl.h2d_argv, true);
         HIPCK(hipGraphAddKernelNode(&cn->h2d, g, nullptr, 0, &kp));
       } else {
         HIPCK(hipGraphAddMemcpyNode1D(&cn->h2d, g, nullptr, 0, sl.base + p.L.in, p.placeholder, p.L.in_cap,
@@ -1166,8 +1176,8 @@ class HipBackend : public Backend {
     if (writes_out(p.t)) {
       // the last stage does
     } else if (out_by_kernel(p.t)) {
-      sl.d2h_copy = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
-      hipKernelNodeParams kp = copy_params(sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
+      sl.d2h_copy.c = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
+      hipKernelNodeParams kp = copy_params(p, sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
       HIPCK(hipGraphAddKernelNode(&cn->d2h, g, &prev, 1, &kp));
     } else {
       HIPCK(hipGraphAddMemcpyNode1D(&cn->d2h, g, &prev, 1, p.placeholder, sl.base + p.L.out, p.L.out_cap,
@@ -1220,8 +1230,8 @@ class HipBackend : public Backend {
     if (writes_out(p.t)) {
       // the last stage does
     } else if (out_by_kernel(p.t)) {
-      sl.d2h_copy = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
-      HIPCK(hipLaunchKernel((const void*)&k_copy_out, dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), sl.d2h_argv, 0, st));
+      sl.d2h_copy.c = CopyArgs{sl.base + p.L.out, p.placeholder, p.L.out_cap};
+      HIPCK(hipLaunchKernel(out_copy(p.t), dim3(d2h_copy_blocks(p.L.out_cap)), dim3(kBlock), sl.d2h_argv, 0, st));
     } else {
       HIPCK(hipMemcpyAsync(p.placeholder, sl.base + p.L.out, p.L.out_cap, hipMemcpyDeviceToHost, st));
     }
@@ -1301,7 +1311,7 @@ class HipBackend : public Backend {
     if (sl.in_bytes && cn.h2d) {
       if (kcopy) {
         sl.h2d_copy = CopyArgs{sl.host_in, sl.base + p.L.in, sl.in_bytes};
-        hipKernelNodeParams kp = copy_params(sl.h2d_argv, true);
+        hipKernelNodeParams kp = copy_params(p, sl.h2d_argv, true);
         HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.h2d, &kp));
       } else {
         HIPCK(hipGraphExecMemcpyNodeSetParams1D(ex, cn.h2d, sl.base + p.L.in, sl.host_in, sl.in_bytes,
@@ -1320,8 +1330,8 @@ class HipBackend : public Backend {
       hipKernelNodeParams kd = kparams(sl, sl.nstages - 1);
       HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[sl.nstages - 1], &kd));
     } else if (out_by_kernel(p.t)) {
-      sl.d2h_copy = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
-      hipKernelNodeParams kd = copy_params(sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
+      sl.d2h_copy.c = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
+      hipKernelNodeParams kd = copy_params(p, sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));
       HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.d2h, &kd));
     } else {
       HIPCK(hipGraphExecMemcpyNodeSetParams1D(ex, cn.d2h, sl.host_out, sl.base + p.L.out, sl.out_bytes,

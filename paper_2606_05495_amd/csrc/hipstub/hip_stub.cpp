@@ -501,6 +501,11 @@ void publish(const SlotConst& sc) {
 
 void k_copy_in(CopyArgs a) { std::memcpy(a.dst, a.src, a.bytes); }
 void k_copy_out(CopyArgs a) { std::memcpy(a.dst, a.src, a.bytes); }
+void k_copy_out_publish(CopyOutArgs a) {
+  std::memcpy(static_cast<char*>(a.c.dst) + 64, static_cast<const char*>(a.c.src) + 64, a.c.bytes - 64);
+  a.sc.outh = static_cast<set_out_header*>(a.c.dst);
+  publish(a.sc);
+}
 void k_ref_copy(RefCopyArgs a) { std::memcpy(a.dst, a.src, a.nvec * 16); }
 void k_done_flag(DoneFlagArgs a) { __atomic_store_n(a.word, a.hdr->seq, __ATOMIC_RELEASE); }
 void k_poison(PoisonArgs a) {
@@ -597,6 +602,7 @@ struct Register {
     using hipstub::register_kernel;
     register_kernel(&k_copy_in);
     register_kernel(&k_copy_out);
+    register_kernel(&k_copy_out_publish);
     register_kernel(&k_ref_copy);
     register_kernel(&k_done_flag);
     register_kernel(&k_poison);

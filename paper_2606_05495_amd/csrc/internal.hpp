@@ -138,6 +138,11 @@ struct TemplateSizes {
   char stage_names[kMaxStages][32];
 };
 
+// Templates whose output copy kernel publishes the header: no stage of theirs
+// runs in one block behind the others.
+inline bool publishes_in_copy(const set_job_template& t) {
+  return t.copy_mode != SET_COPY_NODES && t.pipeline == SET_PIPE_HOTSPOT_F32;
+}
 // Image templates that take the Gaussian and Sobel in one kernel.
 inline bool one_kernel_image(const set_job_template& t) {
   return t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 && !(t.flags & SET_TF_DEBUG) &&

@@ -197,6 +197,14 @@ __global__ __launch_bounds__(kBlock) void k_ref_copy(RefCopyArgs a) {
   if (i < a.nvec) static_cast<uint4*>(a.dst)[i] = static_cast<const uint4*>(a.src)[i];
 }
 __global__ __launch_bounds__(kBlock) void k_copy_out(CopyArgs a) { copy_bytes(a); }
+__global__ __launch_bounds__(kBlock) void k_copy_out_publish(CopyOutArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.sc.outh = static_cast<set_out_header*>(a.c.dst);
+    publish_out(a.sc, true);
+  }
+  copy_bytes(CopyArgs{static_cast<const char*>(a.c.src) + sizeof(set_out_header),
+                      static_cast<char*>(a.c.dst) + sizeof(set_out_header), a.c.bytes - sizeof(set_out_header)});
+}
 
 // ------------------------------------------------------------------ completion word
 // Runs after the job's device-to-host copy node; the kernel boundary orders

@@ -168,6 +168,13 @@ struct CopyArgs {
   void* dst;
   uint64_t bytes;
 };
+// Output copies: k_copy_out_publish writes the header from the slot itself (the
+// stages before it have ended) and copies what follows it.
+struct CopyOutArgs {
+  CopyArgs c;
+  SlotConst sc;
+};
+__global__ void k_copy_out_publish(CopyOutArgs a);
 __global__ void k_copy_in(CopyArgs a);   // host-to-device
 // Bandwidth reference: word i of `nvec` 16-byte words copied by thread i.
 struct RefCopyArgs {
