@@ -516,7 +516,7 @@ int set_run_vector_jobs(set_ctx *c, int template_id, const set_vec_job *jobs, ui
  * job's work-item size taken per size bucket floor(log2 n) from tuning (zero
  * entries and tuning == NULL: the default sizes of set_run_vector_jobs).  A
  * job's S is bit-identical to what set_run_vector_jobs returns for the same
- * (n, item size); the persistent grid (`grid`, 0 = 1024 blocks) changes no
+ * (n, item size); the persistent grid (`grid`, 0 = the library's choice) changes no
  * result.
  *
  * device: HIP device ordinal; made current for the call, then restored.

@@ -34,6 +34,13 @@ constexpr uint32_t kNaMaxJobs = SET_NOALLOC_MAX_JOBS;
 constexpr uint32_t kNaMaxItems = SET_NOALLOC_MAX_ITEMS;
 constexpr int kNaPlanThreads = 1024;
 constexpr int kNaMaxDevices = 64;
+// Blocks of the tile kernel: twice what the device holds at once, so that the
+// dispatcher hands most shares out by itself and few are claimed; or as many as
+// the call can have tiles (a block without one still plans a small call: 4096
+// blocks took one job 14.5 us).  Uneven jobs, us, at 1024 blocks / so: 1024 of up
+// to 8192 elements 29.4 / 26.5, of up to 131072 77 / 70, 256 of up to 2^22 201 /
+// 195, 2048 of up to 2^22 1550 / 1546, one of up to 8192 14.5 / 12.8.
+constexpr uint32_t kNaGrid = 4096;
 
 // Byte offsets inside the static array (each 256-byte aligned).
 constexpr uint64_t kNaHdrOff = 0;        // DevSlotHdr the item kernel stamps
@@ -197,7 +204,8 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     pa.tab = tab;
     pa.work = work;
     pa.split = count * worst_units <= kNaMaxItems;
-    pa.grid = grid ? grid : (uint32_t)kVecBatchGrid;
+    const uint64_t most_tiles = count * (pa.split ? worst_units : worst);
+    pa.grid = grid ? grid : (uint32_t)std::min<uint64_t>(kNaGrid, most_tiles);
     if (count <= (uint64_t)kBlock) {
       VecFewArgs fa{pa, x, y, partials};
       hipLaunchKernelGGL(k_vec_few_tiles, dim3(pa.grid), dim3(kBlock), 0, stream, fa);
