@@ -271,6 +271,7 @@ class HipBackend : public Backend {
                                             p.words + ((size_t)w * d_ + s) * 8};
         if (!copy_streams_.empty() && in_ahead(t) && (cfg_.mode == SET_MODE_SET || s == 0))
           HIPCK(hipEventCreateWithFlags(&sl.in_ev, hipEventDisableTiming));
+        if (one_kernel_image(t)) HIPCK(hipMemset(arrivals(p, sl), 0xFF, arrival_room(p)));
         const uint64_t ch = canary_value(id, w, s, 0), ct = canary_value(id, w, s, 1);
         HIPCK(hipMemcpy(sl.base + p.L.hdr, &ch, 8, hipMemcpyHostToDevice));
         HIPCK(hipMemcpy(sl.base + p.L.tail, &ct, 8, hipMemcpyHostToDevice));
@@ -760,6 +761,14 @@ class HipBackend : public Backend {
     }
   }
 
+  // Arrival words of a one-kernel image template lie where the blurred image
+  // would, which it does not keep: four bytes a pixel, and the words take at most
+  // two a tile, or 256 in all.
+  static uint32_t* arrivals(const Pipe& p, const Slot& sl) { return reinterpret_cast<uint32_t*>(sl.base + p.L.b1); }
+  static uint64_t arrival_room(const Pipe& p) {
+    const Grid3 g = gauss_sobel_grid((int)p.t.height, (int)p.t.width);
+    return arrival_bytes((uint64_t)g.x * g.y);
+  }
   void setup_slot(Pipe& p, Slot& sl, const float taps[3]) {
     const SlotLayout& L = p.L;
     char* b = sl.base;
@@ -824,11 +833,10 @@ class HipBackend : public Backend {
         if (one_kernel_image(t)) {
           const Grid3 g = gauss_sobel_grid(h, w);
           sl.gs = GaussSobelArgs{sl.gauss.in, h, w, taps[0], taps[1], taps[2], sl.sobel.thr, sl.sobel.pcount,
-                                 sl.sobel.psum, sc.hdr, JobScalars{}};
-          sl.sobelf.nparts = g.x * g.y;
+                                 sl.sobel.psum, arrivals(p, sl), (uint32_t*)payload, (float*)(payload + 4), sc.hdr, sc,
+                                 JobScalars{}};
           stage(image_window_path(w) ? (const void*)&k_gauss_sobel_f32<true> : (const void*)&k_gauss_sobel_f32<false>,
                 to_dim3(g), &sl.gs, (unsigned)kGsBlock);
-          stage(wo ? (const void*)&k_copy_out_sobel : (const void*)&k_sobel_final, dim3(1), &sl.sobelf);
           break;
         }
         const bool win = image_window_path(w), full = window_full_width(w);
@@ -963,9 +971,9 @@ class HipBackend : public Backend {
         sl.histf.H = reinterpret_cast<uint32_t*>(o + 64);
         break;
       case SET_PIPE_GAUSS_SOBEL_F32:
-        sl.sobelf.sc.outh = h;
-        sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
-        sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
+        sl.gs.sc.outh = sl.sobelf.sc.outh = h;
+        sl.gs.out_count = sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
+        sl.gs.out_sum = sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
         break;
       case SET_PIPE_SAXPY_TANH_SUM_F32:
         sl.vecf.sc.outh = h;
@@ -1326,9 +1334,11 @@ class HipBackend : public Backend {
         HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[i], &kd));
       }
     }
-    if (writes_out(p.t)) {
+    if (writes_out(p.t) && sl.nstages > 1) {
       hipKernelNodeParams kd = kparams(sl, sl.nstages - 1);
       HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[sl.nstages - 1], &kd));
+    } else if (writes_out(p.t)) {
+      // the one stage's argument block has the output's place
     } else if (out_by_kernel(p.t)) {
       sl.d2h_copy.c = CopyArgs{sl.base + p.L.out, sl.host_out, sl.out_bytes};
       hipKernelNodeParams kd = copy_params(p, sl.d2h_argv, false, d2h_copy_blocks(p.L.out_cap));

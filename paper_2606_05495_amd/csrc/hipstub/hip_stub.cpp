@@ -571,6 +571,7 @@ template void k_sobel_thresh_win_f32<4, false>(SobelArgs);
 template <bool COLUMNS_FIRST>
 void k_gauss_sobel_f32(GaussSobelArgs a) {
   stamp(a.hdr, a.js);
+  publish(a.sc);
 }
 template void k_gauss_sobel_f32<true>(GaussSobelArgs);
 template void k_gauss_sobel_f32<false>(GaussSobelArgs);

@@ -143,13 +143,14 @@ struct TemplateSizes {
 inline bool publishes_in_copy(const set_job_template& t) {
   return t.copy_mode != SET_COPY_NODES && t.pipeline == SET_PIPE_HOTSPOT_F32;
 }
-// Image templates that take the Gaussian and Sobel in one kernel.
+// Image templates that take the Gaussian and Sobel in one kernel, whose last block
+// publishes the output.
 inline bool one_kernel_image(const set_job_template& t) {
   return t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 && !(t.flags & SET_TF_DEBUG) &&
          gauss_sobel_in_one((int)t.height, (int)t.width);
 }
-// Templates whose last stage, a kernel of one block, writes the job's output to
-// host memory itself: small outputs without intermediate images, of copy modes
+// Templates whose last stage writes the job's output to host memory itself, from
+// the one block that has all of it: small outputs without intermediate images, of copy modes
 // whose output copy is a kernel.
 inline bool writes_out(const set_job_template& t) {
   return t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG) &&

@@ -65,6 +65,59 @@ __device__ inline void complete_out(const SlotConst& sc, uint64_t seq) {
   if (threadIdx.x == 0) __hip_atomic_store(sc.word, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Blocks' arrivals at the end of a kernel whose last block to arrive finishes the
+// job; the others leave their partial results and are done.  A word counts up to
+// kArriveGroup blocks and, in a launch of more, one at the root the groups' last
+// blocks: one word takes about 70 additions a microsecond, so every group's is in
+// lines of its own.  A word rests at all ones, which a poisoned slot holds too,
+// and the last to arrive puts it back.
+//
+// Partials are stored and read by relaxed agent-scope operations (put_partial,
+// get_partial), which act where the XCDs' caches meet; every wave waits for the
+// acknowledgement of its stores before the block arrives.  A release fence
+// would write the XCD's whole L2 back instead.
+template <typename T>
+__device__ inline void put_partial(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T get_partial(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool arrive(uint32_t* word, uint32_t count) {
+  const uint32_t before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool last = before + 2u == count;  // the first to arrive finds all ones
+  if (last) __hip_atomic_store(word, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return last;
+}
+// All threads of block b of nblocks, behind their put_partials.
+__device__ inline bool arrives_last(uint32_t* words, uint32_t b, uint32_t nblocks) {
+  __shared__ uint32_t s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t g = b / kArriveGroup, first = g * kArriveGroup;
+    const uint32_t in_group = nblocks - first < kArriveGroup ? nblocks - first : kArriveGroup;
+    bool last = arrive(words + (size_t)g * (kArriveBytes / 4), in_group);
+    if (last && nblocks > kArriveGroup)
+      last = arrive(words + kArriveBytes / 8, (nblocks + kArriveGroup - 1) / kArriveGroup);
+    s_last = last ? 1u : 0u;
+  }
+  __syncthreads();
+  return s_last != 0;
+}
+// The output header of the job whose scalars a kernel carries itself (the slot's
+// copy of them was written by another block of it).
+__device__ inline OutWords load_out(const SlotConst& sc, const JobScalars& js) {
+  OutWords w;
+  w.h.job_id = js.job_id;
+  w.h.seq = js.seq;
+  w.h.user_tag = js.user_tag;
+  w.h.worker = js.worker;
+  w.h.slot = js.slot;
+  w.canaries = (sc.hdr->canary_head == sc.canary_head) & (*sc.tail == sc.canary_tail);
+  return w;
+}
 
 __device__ inline float wave_sum_f32(float v) {
 #pragma unroll
@@ -494,7 +547,14 @@ __global__ __launch_bounds__(kBlock) void k_sobel_thresh_f32(SobelArgs a) {
 // LDS-tile kernels.  A block's partials are those of its tile.
 // Small images are launch and memory latency, which one kernel pays once: a
 // 333 x 250 image 4.8 + 4.6 us as two kernels, four such jobs one after another
-// 117 -> 103 us.
+// 117 -> 103 us.  The tiles' partials are combined by the block that arrives last,
+// which takes as long as a one-block kernel behind this one but is a launch less,
+// where launches by one dispatcher thread set the pace: 64 jobs of 64 x 64 805-916
+// -> 608-648 us, 16 of 333 x 250 266 -> 225, one after another and from 512 x 400
+// up no difference.  Box/histogram and vector jobs have several threads that
+// launch and mostly one job in flight to a worker: there it went neither way for
+// the first, and 256 of the second, whose last block waits behind all the reads of
+// the others, took 910 us and not 790.
 template <bool COLUMNS_FIRST>
 __global__ __launch_bounds__(kGsBlock) void k_gauss_sobel_f32(GaussSobelArgs a) {
   constexpr int BW = kSobelTW + 2, BH = kSobelTH + 2;  // blurred tile with its ring
@@ -570,8 +630,8 @@ __global__ __launch_bounds__(kGsBlock) void k_gauss_sobel_f32(GaussSobelArgs a) 
     s_count[tid >> 6] = wc;
   }
   __syncthreads();
+  const unsigned b = blockIdx.y * gridDim.x + blockIdx.x, nparts = gridDim.x * gridDim.y;
   if (tid == 0) {
-    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
     float s = 0.f;
     uint32_t n = 0;
 #pragma unroll
@@ -579,9 +639,52 @@ __global__ __launch_bounds__(kGsBlock) void k_gauss_sobel_f32(GaussSobelArgs a) 
       s += s_sum[k];
       n += s_count[k];
     }
-    a.psum[b] = s;
-    a.pcount[b] = n;
+    put_partial(&a.psum[b], s);
+    put_partial(&a.pcount[b], n);
   }
+  if (!arrives_last(a.arrivals, b, nparts)) return;
+  // The tiles' partials: thread t takes tiles t, t + kGsBlock, ..., four loads
+  // of each going out together.
+  OutWords w{};
+  if (tid == 0) w = load_out(a.sc, a.js);
+  sum = 0.f;
+  cnt = 0;
+  for (unsigned k = tid; k < nparts; k += 4 * kGsBlock) {
+    float f[4];
+    uint32_t u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned q = k + i * kGsBlock < nparts ? k + i * kGsBlock : nparts - 1;
+      f[i] = get_partial(&a.psum[q]);
+      u[i] = get_partial(&a.pcount[q]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (k + i * kGsBlock < nparts) {
+        sum += f[i];
+        cnt += u[i];
+      }
+  }
+  sum = wave_total_f32(sum);
+  cnt = wave_total_u32(cnt);
+  if ((tid & 63) == 0) {
+    s_sum[tid >> 6] = sum;
+    s_count[tid >> 6] = cnt;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    sum = 0.f;
+    cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kGsBlock / 64; ++k) {
+      sum += s_sum[k];
+      cnt += s_count[k];
+    }
+    *a.out_count = cnt;
+    *a.out_sum = sum;
+    store_out(a.sc, w, true);
+  }
+  complete_out(a.sc, w.h.seq);
 }
 template __global__ void k_gauss_sobel_f32<true>(GaussSobelArgs a);
 template __global__ void k_gauss_sobel_f32<false>(GaussSobelArgs a);

@@ -83,7 +83,11 @@ struct GaussSobelArgs {
   float thr;
   uint32_t* pcount;    // [grid]
   float* psum;         // [grid]
+  uint32_t* arrivals;  // arrival_bytes(grid)
+  uint32_t* out_count; // output payload
+  float* out_sum;
   DevSlotHdr* hdr;
+  SlotConst sc;
   JobScalars js;
 };
 struct VecArgs {

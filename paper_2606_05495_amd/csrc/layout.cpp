@@ -308,8 +308,7 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
       if (one_kernel_image(t)) {
         const Grid3 g = gauss_sobel_grid((int)t.height, (int)t.width);
         const uint64_t nt = (uint64_t)g.x * g.y;
-        stage("gauss_sobel_f32", 4 * npix + 8 * nt);
-        stage("sobel_final", 8 * nt + 8 + 64);
+        stage("gauss_sobel_f32", 4 * npix + 2 * 8 * nt + 8 + 64);
         break;
       }
       const uint64_t nb = sobel_partials((int)t.height, (int)t.width);

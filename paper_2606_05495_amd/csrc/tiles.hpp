@@ -20,6 +20,13 @@ constexpr int kGaussTW = 64, kGaussTH = 16;   // separable Gaussian: output tile
 constexpr int kSobelTW = 64, kSobelTH = 16;   // Sobel: output tile
 constexpr int kVecChunk = 2048;               // vector job: elements per block (multiple of 4*kBlock)
 constexpr int kVecGridCap = 2048;             // vector job: most blocks per job
+// Words that count a launch's blocks as they arrive: one to a group of blocks,
+// in kArriveBytes of its own; the root is in the first group's.
+constexpr unsigned kArriveGroup = 128;
+constexpr unsigned kArriveBytes = 256;
+SETRT_HD inline uint64_t arrival_bytes(uint64_t blocks) {
+  return (blocks + kArriveGroup - 1) / kArriveGroup * kArriveBytes;
+}
 constexpr int kScanItems = 8;                 // scan: items per thread
 constexpr int kScanTile = kBlock * kScanItems;
 constexpr int kCopyBlocks = 32;               // host<->device copy kernels: small grid, PCIe-bound
