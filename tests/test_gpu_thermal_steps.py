@@ -42,3 +42,32 @@ def test_steps_per_launch(torch_gpu, shape):
         got = nout[64:].view(np.float32).reshape(h, w)
         ref = oracle.hotspot(t0, p, steps)
         assert np.max(np.abs(got - ref)) <= oracle.hotspot_tolerance(ref, steps), (shape, steps)
+
+
+@pytest.mark.parametrize("case", [(256, 256, 16), (250, 333, 1), (260, 516, 1), (2048, 2048, 1), (700, 771, 9)])
+def test_rounding_is_below_the_formula_as_it_stands(torch_gpu, case):
+    """The steps' rounding error, root mean square against float64, is below that
+    of the update formula evaluated term by term in float32: it rounds the
+    temperature once a step, the formula four times."""
+    h, w, steps = case
+    print("thermal rounding", case)
+    sys.stdout.flush()
+    t0, p = synth.hotspot_input(8, h * 1000 + w, h, w)
+    ib, ob = 8 * h * w, 64 + 4 * h * w
+    tin, nin = pinned(ib)
+    tout, nout = pinned(ob)
+    nin[:ib].view(np.float32)[:] = np.concatenate([t0.ravel(), p.ravel()])
+    with Context(mode="sync", workers=1, slots=1) as ctx:
+        tid = ctx.define("hotspot", width=w, height=h, max_n=steps)
+        ctx.submit(tid, host_in=tin.data_ptr(), in_bytes=ib, host_out=tout.data_ptr(), out_bytes=ob)
+        ctx.drain()
+    got = nout[64:ob].view(np.float32).reshape(h, w)
+    f = np.float32
+    t, p = t0.astype(f).reshape(h, w), p.astype(f).reshape(h, w)
+    for _ in range(steps):
+        e = np.pad(t, 1, mode="edge")
+        lap_y, lap_x = (e[:-2, 1:-1] + e[2:, 1:-1]) - 2 * t, (e[1:-1, :-2] + e[1:-1, 2:]) - 2 * t
+        t = t + f(0.5) * p + f(0.1) * lap_y + f(0.1) * lap_x + f(1 / 640) * (f(300) - t)
+    ref = oracle.hotspot(t0, p, steps)
+    rms = lambda v: float(np.sqrt(np.mean((v.astype(np.float64) - ref) ** 2)))
+    assert t.dtype == np.float32 and rms(got) < rms(t)
