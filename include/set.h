@@ -7,7 +7,9 @@
  * chain of short kernels and a device-to-host copy (Section 3.2).  Each job
  * is replayed as a pre-instantiated graph executable bound to one worker's
  * stream and buffers (Section 4.1, "Job-as-Graph and Memory Management";
- * Section 4.2 (1) "Workers").  A submitter thread binds per-job parameters
+ * Section 4.2 (1) "Workers"); the few kernels of a short job are launched one
+ * by one instead, where that costs the dispatcher less than a graph launch.  A
+ * submitter thread binds per-job parameters
  * and pushes ready executables into per-worker queues (Algorithm 1); a
  * dispatcher thread pairs free workers with jobs, stealing from other
  * workers' queues when its own is empty and retargeting a stolen job to the
@@ -102,15 +104,16 @@ enum set_callback_mode {
     SET_CB_EVENT_CHAIN = 1,
     /* hipLaunchHostFunc directly on the worker stream after the graph. */
     SET_CB_SAME_STREAM = 2,
-    /* The job's graph ends with a one-thread kernel node that stores the
-     * job's binding sequence number into the slot's word of a pinned host
-     * array (system-scope release store, after the device-to-host copy node
-     * has finished).  The completion thread watches each worker's oldest
+    /* The job's last kernel stores the job's binding sequence number into the
+     * slot's word of a pinned host array (a system-scope release store, after
+     * the job's output has reached host memory): the stage that writes the
+     * output there itself, or else a one-thread kernel behind the output copy.
+     * The completion thread watches each worker's oldest
      * word with plain host loads and calls no HIP function, so it never
      * contends with the dispatcher inside the HIP runtime.  SET mode only.
-     * Faster than event polling for short jobs with copy kernels; with DMA
-     * input copies the extra kernel costs more than it saves, and event
-     * polling is the faster. */
+     * Faster than event polling for short jobs with copy kernels; where the
+     * extra kernel is needed and the input goes by DMA it costs more than it
+     * saves, and event polling is the faster. */
     SET_CB_HOST_FLAG = 3,
     /* hipEventRecord on the worker stream after the job's graph, with the
      * slot's events created hipEventBlockingSync; one library thread per
@@ -179,8 +182,9 @@ enum set_pipeline {
      * number of explicit steps K (1..32), one or several to a kernel of the chain:
      *   T' = T + 0.5*P + 0.1*(N + S - 2T) + 0.1*(W + E - 2T) + (300 - T)/640
      * with N, S, W, E the four neighbours and a neighbour outside the grid
-     * taken as the cell itself (no heat crosses the border); then a kernel
-     * publishing the header.  out: set_out_header + T_K (float32, row-major). */
+     * taken as the cell itself (no heat crosses the border).  The header is
+     * published by the output copy kernel, or by a kernel ahead of a memcpy
+     * node.  out: set_out_header + T_K (float32, row-major). */
     SET_PIPE_HOTSPOT_F32 = 6
 };
 
@@ -188,6 +192,8 @@ enum set_pipeline {
 enum set_copy_mode {
     SET_COPY_KERNELS = 0, /* small-grid copy kernels, nodes of the job's graph, that pull the input from /
                              push the output to pinned host memory; host buffers must be 16-byte aligned.
+                             Small outputs (a histogram, a count and a sum; without SET_TF_DEBUG) have no
+                             copy: the last stage writes them to the host buffer, also in SET_COPY_ASYNC_IN.
                              Default: ROCm runs graph memcpy nodes as large-grid blit kernels that crowd
                              out the stage kernels */
     SET_COPY_NODES = 1,   /* graph memcpy nodes (hipMemcpyAsync in the synchronous model) */
@@ -225,7 +231,8 @@ typedef struct set_config {
     int32_t backend;             /* enum set_backend */
     int32_t device;              /* HIP device ordinal */
     int32_t num_workers;         /* b: workers, one stream each (Section 4.2 (1)); 1..256 */
-    int32_t slots_per_worker;    /* d: buffer slots (one graph exec each) per worker; 1..64 */
+    int32_t slots_per_worker;    /* d: buffer slots (with a graph exec each, where graphs are replayed) per worker;
+                                    1..64 */
     int32_t queue_capacity;      /* capacity of each per-worker queue Q_i; 0 = max(1, d - inflight) */
     int32_t inflight_per_worker; /* launch permits per worker in the free pool; 0 = min(2, d) */
     int32_t work_stealing;       /* 1: FindJob steals from (w+k) mod b (Algorithm 2); 0: local only */
@@ -408,7 +415,10 @@ int set_template_footprint(const set_config *cfg, const set_job_template *t,
 /* Define a job template: lay out one buffer slot per (worker, slot) in the
  * arena and build + instantiate + upload one graph per slot whose nodes hold
  * placeholders for per-job arguments (Section 4.1).  In batch-sync mode the
- * batch graph is built instead.  *template_id receives the id (0, 1, ...).
+ * batch graph is built instead.  In SET mode no graph is built for a template
+ * whose jobs are at most six launches, copy less than 1 MiB in all and have
+ * their output written by a kernel, unless it asks for a captured graph
+ * (SET_TF_CAPTURE, library calls): its kernels are launched directly.  *template_id receives the id (0, 1, ...).
  * Must be called before any submit of that template. */
 int set_template_define(set_ctx *c, const set_job_template *t, int *template_id);
 
@@ -473,7 +483,7 @@ int set_get_job_times(set_ctx *c, set_job_times *out, uint64_t max, uint64_t *co
  * times the template's host-to-device / device-to-host copy of its largest
  * job (Eq. 1's t_in and t_out) the way a job performs it (copy kernel or DMA)
  * against a library-owned pinned buffer; 0 us for a pipeline without that
- * copy.  Requires a drained context. */
+ * copy, and for the output where the last stage writes it to host memory.  Requires a drained context. */
 #define SET_STAGE_INPUT_COPY (-1)
 #define SET_STAGE_OUTPUT_COPY (-2)
 int set_time_stage(set_ctx *c, int template_id, int stage, int worker, int reps, double *avg_us);

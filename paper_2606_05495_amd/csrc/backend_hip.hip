@@ -1,8 +1,9 @@
 // HIP backend: job templates become per-(worker, slot) graph executables
-// (H2D memcpy node -> stage kernel nodes -> D2H memcpy node, Section 4.1),
-// bound per job by updating the executable's memcpy endpoints and the first
-// kernel's argument block (UpdateGraphParams), launched on the worker's
-// stream with a completion callback (GraphLaunch + AddCallback, Algorithm 2).
+// (H2D copy node -> stage kernel nodes -> D2H copy node, Section 4.1), bound
+// per job by updating the executable's copy endpoints and the first kernel's
+// argument block (UpdateGraphParams), launched on the worker's stream with a
+// completion callback (GraphLaunch + AddCallback, Algorithm 2).  In SET mode a
+// short job's chain is launched kernel by kernel instead (launches_directly).
 // The same slots and kernels serve the comparison systems of Section 5.1
 // (direct launches, per-job graph relaunch, one batch graph of b chains).
 #include <hip/hip_runtime.h>

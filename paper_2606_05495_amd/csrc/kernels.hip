@@ -4,13 +4,14 @@
 // job's input and size (bit-identical whatever stream, slot or neighbour ran
 // beside it); the histogram uses LDS atomics on per-wave private bins.
 //
-// Cross-block results are combined by a separate single-block kernel node
-// that runs after the producing kernel has finished (the kernel boundary is
-// the only synchronisation: no per-block device-scope fences, which on this
-// multi-XCD part write back the issuing XCD's L2 and cost tens of
-// microseconds when a thousand blocks issue them).  That last kernel combines
-// the per-block partials in block order, checks the slot's canaries and
-// publishes the output header.
+// Cross-block results are combined by a separate single-block kernel that runs
+// after the producing kernel has finished (the kernel boundary is the
+// synchronisation: no per-block device-scope fences, which on this multi-XCD
+// part write back the issuing XCD's L2 and cost tens of microseconds when a
+// thousand blocks issue them).  The one-kernel images alone leave it to the block
+// that arrives last, by agent-scope stores and loads without a fence.  What
+// combines the per-block partials does so in a fixed order, checks the slot's
+// canaries and publishes the output header.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -55,8 +56,8 @@ __device__ inline void store_out(const SlotConst& sc, const OutWords& w, bool ex
 }
 __device__ inline void publish_out(const SlotConst& sc, bool extra_ok) { store_out(sc, load_out(sc), extra_ok); }
 
-// End of a one-block kernel that wrote the job's output to host memory itself:
-// where the template completes by words, the word is stored once every wave's
+// End of a kernel, by the one block that wrote the job's output to host memory
+// itself: where the template completes by words, the word is stored once every wave's
 // stores have been acknowledged.  All threads of the block.
 __device__ inline void complete_out(const SlotConst& sc, uint64_t seq) {
   if (!sc.word) return;
