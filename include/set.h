@@ -161,7 +161,7 @@ enum set_pipeline {
      * work-item size) -> a persistent
      * kernel whose blocks pull (job, tile) work items, or equal parts of them,
      * from an atomic counter -> a kernel summing each job's tile partials in
-     * a fixed order -> D2H of
+     * a fixed order -> D2H (by that kernel where batch_max is at most 1024) of
      * set_out_header + one float32 S per job, in descriptor order.  Jobs are
      * normally submitted through set_run_vector_jobs, which builds the
      * tables; per-job S depends only on (n, tile size). */
@@ -192,7 +192,7 @@ enum set_pipeline {
 enum set_copy_mode {
     SET_COPY_KERNELS = 0, /* small-grid copy kernels, nodes of the job's graph, that pull the input from /
                              push the output to pinned host memory; host buffers must be 16-byte aligned.
-                             Small outputs (a histogram, a count and a sum; without SET_TF_DEBUG) have no
+                             Small outputs (a histogram, sums, a batch's results; without SET_TF_DEBUG) have no
                              copy: the last stage writes them to the host buffer, also in SET_COPY_ASYNC_IN.
                              Default: ROCm runs graph memcpy nodes as large-grid blit kernels that crowd
                              out the stage kernels */

@@ -272,7 +272,7 @@ class HipBackend : public Backend {
                                             p.words + ((size_t)w * d_ + s) * 8};
         if (!copy_streams_.empty() && in_ahead(t) && (cfg_.mode == SET_MODE_SET || s == 0))
           HIPCK(hipEventCreateWithFlags(&sl.in_ev, hipEventDisableTiming));
-        if (one_kernel_image(t)) HIPCK(hipMemset(arrivals(p, sl), 0xFF, arrival_room(p)));
+        if (arrives(p)) HIPCK(hipMemset(arrivals(p, sl), 0xFF, arrival_room(p)));
         const uint64_t ch = canary_value(id, w, s, 0), ct = canary_value(id, w, s, 1);
         HIPCK(hipMemcpy(sl.base + p.L.hdr, &ch, 8, hipMemcpyHostToDevice));
         HIPCK(hipMemcpy(sl.base + p.L.tail, &ct, 8, hipMemcpyHostToDevice));
@@ -764,9 +764,17 @@ class HipBackend : public Backend {
 
   // Arrival words of a one-kernel image template lie where the blurred image
   // would, which it does not keep: four bytes a pixel, and the words take at most
-  // two a tile, or 256 in all.
-  static uint32_t* arrivals(const Pipe& p, const Slot& sl) { return reinterpret_cast<uint32_t*>(sl.base + p.L.b1); }
+  // two a tile, or 256 in all.  A vector batch's lie where its output would, 16
+  // bytes a block of its last kernel.
+  static bool arrives(const Pipe& p) {
+    return one_kernel_image(p.t) || (p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32 && writes_out(p.t));
+  }
+  static uint32_t* arrivals(const Pipe& p, const Slot& sl) {
+    return reinterpret_cast<uint32_t*>(sl.base + (p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32 ? p.L.out : p.L.b1));
+  }
   static uint64_t arrival_room(const Pipe& p) {
+    if (p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32)
+      return arrival_bytes((p.t.batch_max + kVecFinalJobs - 1) / kVecFinalJobs);
     const Grid3 g = gauss_sobel_grid((int)p.t.height, (int)p.t.width);
     return arrival_bytes((uint64_t)g.x * g.y);
   }
@@ -872,8 +880,8 @@ class HipBackend : public Backend {
         uint32_t* work = (uint32_t*)(b + L.scratch + q);
         sl.vb = VecBatchArgs{(const uint8_t*)(b + L.in), t.dev_x_pool, t.dev_y_pool, (float*)(b + L.scratch), work,
                              sc.hdr, JobScalars{}};
-        sl.vbf = VecBatchFinalArgs{(const uint8_t*)(b + L.in), (const float*)(b + L.scratch), work,
-                                   (float*)(b + L.out + 64), sc};
+        sl.vbf = VecBatchFinalArgs{(uint8_t*)(b + L.in), (const float*)(b + L.scratch), work, (float*)payload, sc,
+                                   wo ? arrivals(p, sl) : nullptr, 0};
         const int vbb = vec_batch_block(t);
         const void* vbk = vbb == 128   ? (const void*)&k_vec_batch_tiles<128>
                           : vbb == 512 ? (const void*)&k_vec_batch_tiles<512>
@@ -976,6 +984,10 @@ class HipBackend : public Backend {
         sl.gs.out_count = sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
         sl.gs.out_sum = sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
         break;
+      case SET_PIPE_SAXPY_BATCH_F32:
+        sl.vbf.sc.outh = h;
+        sl.vbf.results = reinterpret_cast<float*>(o + 64);
+        break;
       case SET_PIPE_SAXPY_TANH_SUM_F32:
         sl.vecf.sc.outh = h;
         sl.vecf.out_sum = reinterpret_cast<float*>(o + 64);
@@ -1051,6 +1063,10 @@ class HipBackend : public Backend {
       case SET_PIPE_SAXPY_BATCH_F32:
         sl.vb.js = js;
         sl.grid[0] = dim3(j->args.grid ? j->args.grid : (p.t.grid > 0 ? (unsigned)p.t.grid : (unsigned)kVecBatchGrid));
+        if (writes_out(p.t)) {
+          sl.vbf.n = (uint32_t)js.n;
+          sl.grid[1] = dim3((sl.vbf.n + kVecFinalJobs - 1) / kVecFinalJobs);
+        }
         break;
     }
     sl.host_in = j->args.host_in;

@@ -90,7 +90,7 @@ struct VecBatchDesc {
   uint32_t tile_elems;   // elements per tile, multiple of 256
   uint32_t unit_elems;   // elements per unit: tile_elems, or an equal part of it
   uint32_t per_item;     // tiles per work item
-  uint32_t pad;
+  float sum;             // the job's result, on its way to the block that collects them
 };
 // Tile geometry of a job of n elements with work items of item_elems, for
 // blocks of `block` threads; split: tiles are units.
@@ -100,7 +100,7 @@ SETRT_HD inline void vec_set_tiles(VecBatchDesc& d, uint32_t n, uint32_t item_el
   d.tile_elems = split ? d.unit_elems : item_elems;
   d.per_item = item_elems / d.tile_elems;
   d.ntiles = (uint32_t)(((uint64_t)n + d.tile_elems - 1) / d.tile_elems);
-  d.pad = 0;
+  d.sum = 0.f;
 }
 inline uint64_t vec_units(uint64_t n, uint32_t item_elems, int block) {
   const uint32_t u = vec_unit_elems(item_elems, block);
@@ -155,7 +155,8 @@ inline bool one_kernel_image(const set_job_template& t) {
 inline bool writes_out(const set_job_template& t) {
   return t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG) &&
          (t.pipeline == SET_PIPE_BOX_HIST_U8 || t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 ||
-          t.pipeline == SET_PIPE_SAXPY_TANH_SUM_F32);
+          t.pipeline == SET_PIPE_SAXPY_TANH_SUM_F32 ||
+          (t.pipeline == SET_PIPE_SAXPY_BATCH_F32 && t.batch_max <= kVecFinishJobs));
 }
 // Static per-job sizes of a template (in/out bytes for a job with length n).
 uint64_t pipeline_in_bytes(const set_job_template& t, uint64_t n);

@@ -8,8 +8,9 @@
 // after the producing kernel has finished (the kernel boundary is the
 // synchronisation: no per-block device-scope fences, which on this multi-XCD
 // part write back the issuing XCD's L2 and cost tens of microseconds when a
-// thousand blocks issue them).  The one-kernel images alone leave it to the block
-// that arrives last, by agent-scope stores and loads without a fence.  What
+// thousand blocks issue them).  The one-kernel images and the last kernel of vector
+// batches leave it to the block that arrives last, by agent-scope stores and loads
+// without a fence.  What
 // combines the per-block partials does so in a fixed order, checks the slot's
 // canaries and publishes the output header.
 #include <type_traits>
@@ -1678,19 +1679,34 @@ __global__ __launch_bounds__(kBlock, 8) void k_vec_few_tiles(VecFewArgs a) {
 }
 
 // Job j = wave: its tiles' partials in a fixed order.  Block 0 also rewinds the
-// work counter for the slot's next batch and publishes the header.
+// work counter for the slot's next batch and publishes the header; or, where the
+// output is small and goes to host memory, the block that arrives last does, with
+// every job's result, which saves a batch its copy and its completion kernel:
+// calls of 2 jobs 76 -> 68 us, 4 (as many batches) 117 -> 99, 64 196 -> 188, 1024
+// 833 -> 816.
 __global__ __launch_bounds__(kBlock) void k_vec_batch_final(VecBatchFinalArgs a) {
   const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
-  const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
+  VecBatchDesc* D = reinterpret_cast<VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
   const uint32_t j = blockIdx.x * kVecFinalJobs + (threadIdx.x >> 6);
+  OutWords w{};
+  if (threadIdx.x == 0) w = load_out(a.sc);
   if (j < H->count) {
     const float s = vec_job_total(a.partials + D[j].tile_start, D[j].ntiles, D[j].per_item);
-    if ((threadIdx.x & 63) == 0) a.results[j] = s;
+    if ((threadIdx.x & 63) == 0) {
+      if (a.arrivals)
+        put_partial(&D[j].sum, s);
+      else
+        a.results[j] = s;
+    }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (a.arrivals ? !arrives_last(a.arrivals, blockIdx.x, gridDim.x) : blockIdx.x != 0) return;
+  if (a.arrivals)
+    for (uint32_t k = threadIdx.x; k < a.n; k += kBlock) a.results[k] = get_partial(&D[k].sum);
+  if (threadIdx.x == 0) {
     *a.work = 0u;
-    publish_out(a.sc, true);
+    store_out(a.sc, w, true);
   }
+  complete_out(a.sc, w.h.seq);
 }
 
 // ------------------------------------------------------------------ inclusive scan int32 -> int64

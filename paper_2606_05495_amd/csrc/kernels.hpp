@@ -131,11 +131,13 @@ struct VecFewArgs {
 };
 __global__ void k_vec_few_tiles(VecFewArgs a);
 struct VecBatchFinalArgs {
-  const uint8_t* tab;
+  uint8_t* tab;
   const float* partials;
   uint32_t* work;
   float* results;      // output payload, one float per job
   SlotConst sc;
+  uint32_t* arrivals;  // where the last block writes the output (arrival_bytes(grid)), or null
+  uint32_t n;          // results it writes
 };
 // Scan as reduce -> spine -> downsweep; all three are launched with the grid
 // of the template's largest n, so a job of any length needs no grid update.

@@ -73,6 +73,10 @@ SETRT_HD inline uint32_t vec_claim(uint64_t elems, uint32_t units, uint32_t grid
 }
 constexpr int kVecUnitsPerItem = 4;  // most units of one work item
 constexpr int kVecFinalJobs = 4;     // jobs per block of the batch's last kernel: one wave each
+// Up to this many jobs to a batch, the last block of that kernel writes the results
+// to host memory, four to a thread; longer ones are left to the copy kernel's 32
+// blocks.
+constexpr uint32_t kVecFinishJobs = 1024;
 
 struct Grid3 {
   unsigned x, y, z;

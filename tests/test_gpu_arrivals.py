@@ -88,3 +88,31 @@ def test_images(torch_gpu, tiles):
         for i, out in enumerate(outs):
             assert int(out[64:68].view(np.uint32)[0]) == counts[i % 3], (way, i)
             assert out[68:72].tobytes() == sums[i % 3], (way, i)
+
+
+@pytest.mark.parametrize("way", ["direct", "direct, poisoned", "captured", "memcpy nodes"])
+@pytest.mark.parametrize("room", [1, 5, 1024, 1025])
+def test_vector_batches(torch_gpu, room, way):
+    """Batches of one job to a full table, above and below the size up to which
+    the last block writes the results itself, several through each slot.  The
+    vectors' values are 0 and +-1 and tanh(16) is one in float32, so every sum is
+    a whole number and exact."""
+    rng = np.random.default_rng(room)
+    x = rng.integers(-1, 2, 1 << 22).astype(np.float32)
+    xd = torch_gpu.from_numpy(x).cuda()
+    yd = torch_gpu.zeros_like(xd)
+    ctx, t = _context(way)
+    with ctx:
+        tid = ctx.define("saxpy_batch", max_n=1 << 16, x_pool=xd, y_pool=yd, batch_max=room, tiles_max=4 * room + 64, **t)
+        for count in sorted({1, 4, 5, 511, 513, room - 1, room, 5 * room + 1} - {0}):
+            if count > 8 * room:
+                continue
+            print("arrivals: vector batches of up to", room, way, count)
+            sys.stdout.flush()
+            v = np.zeros(count, A.VEC_JOB_DTYPE)
+            v["n"] = rng.integers(1024, 2048, count)
+            v["x_off"] = rng.integers(0, len(x) - 2048, count)
+            v["a"] = 16.0
+            got, batches = ctx.run_vector_jobs(tid, v)
+            want = [x[o:o + n].astype(np.int64).sum() for o, n in zip(v["x_off"].tolist(), v["n"].tolist())]
+            assert batches == -(-count // room) and np.array_equal(got, np.array(want, np.float32)), count
