@@ -99,7 +99,7 @@ SETRT_HD inline void vec_set_tiles(VecBatchDesc& d, uint32_t n, uint32_t item_el
   d.unit_elems = vec_unit_elems(item_elems, block);
   d.tile_elems = split ? d.unit_elems : item_elems;
   d.per_item = item_elems / d.tile_elems;
-  d.ntiles = (uint32_t)(((uint64_t)n + d.tile_elems - 1) / d.tile_elems);
+  d.ntiles = n ? (n - 1) / d.tile_elems + 1 : 0;
   d.sum = 0.f;
 }
 inline uint64_t vec_units(uint64_t n, uint32_t item_elems, int block) {

@@ -132,17 +132,6 @@ __device__ inline uint32_t wave_sum_u32(uint32_t v) {
   return v;
 }
 
-__device__ inline uint32_t wave_total_u32(uint32_t v) {
-  int x = (int)v;
-  x += dpp_i<0xb1>(x);
-  x += dpp_i<0x4e>(x);
-  x += dpp_i<0x141>(x);
-  x += dpp_i<0x140>(x);
-  x += dpp_i<0x142, 0xa>(x);
-  x += dpp_i<0x143, 0xc>(x);
-  return (uint32_t)__builtin_amdgcn_readlane(x, 63);
-}
-
 // Block sums in a fixed order: lane 0 of each wave, then waves 0..3 pairwise.
 // Every thread returns the same value.
 __device__ inline float block_sum_f32(float v, float* s4) {
@@ -1648,12 +1637,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_vec_few_tiles(VecFewArgs a) {
   const uint32_t j = threadIdx.x, lane = j & 63u, wave = j >> 6;
   VecBatchDesc d{};
   if (j < a.plan.count) d = vec_plan_job(a.plan, a.plan.jobs[j]);
-  uint32_t upto = d.ntiles;  // inclusive prefix within the wave, then over the waves
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t u = __shfl_up(upto, off, 64);
-    if (lane >= (uint32_t)off) upto += u;
-  }
+  const uint32_t upto = wave_inclusive_u32(d.ntiles);  // within the wave, then over the waves
   if (lane == 63) s_wave[wave] = upto;
   __syncthreads();
   uint32_t before = 0, T = 0;

@@ -286,9 +286,31 @@ __global__ void k_copy_out_vec(VecFinalArgs a);
 // rows 1 and 3 and row_bcast:31 into rows 2 and 3; lane 63 ends with the total,
 // which readlane returns to every lane.  Lanes of rows a broadcast leaves out
 // add the old value 0.  The order of the additions is fixed.
-template <int CTRL, int ROWS = 0xf>
+template <int CTRL, int ROWS = 0xf, int BANKS = 0xf>
 __device__ inline int dpp_i(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, BANKS, false);
+}
+__device__ inline uint32_t wave_total_u32(uint32_t v) {
+  int x = (int)v;
+  x += dpp_i<0xb1>(x);
+  x += dpp_i<0x4e>(x);
+  x += dpp_i<0x141>(x);
+  x += dpp_i<0x140>(x);
+  x += dpp_i<0x142, 0xa>(x);
+  x += dpp_i<0x143, 0xc>(x);
+  return (uint32_t)__builtin_amdgcn_readlane(x, 63);
+}
+// Inclusive prefix sum over the wave: the inputs 1, 2 and 3 lanes below (each lane
+// then holds its 4-lane window's sum), row_shr:4 and 8 into the upper banks, the
+// totals of the rows below by row_bcast.
+__device__ inline uint32_t wave_inclusive_u32(uint32_t in) {
+  const int x = (int)in;
+  int v = x + dpp_i<0x111>(x) + dpp_i<0x112>(x) + dpp_i<0x113>(x);
+  v += dpp_i<0x114, 0xf, 0xe>(v);
+  v += dpp_i<0x118, 0xf, 0xc>(v);
+  v += dpp_i<0x142, 0xa>(v);
+  v += dpp_i<0x143, 0xc>(v);
+  return (uint32_t)v;
 }
 __device__ inline float wave_total_f32(float v) {
   v += __int_as_float(dpp_i<0xb1>(__float_as_int(v)));        // quad_perm [1,0,3,2]
