@@ -531,7 +531,7 @@ int set_run_vector_jobs(set_ctx *c, int template_id, const set_vec_job *jobs, ui
  *
  * device: HIP device ordinal; made current for the call, then restored.
  * stream: hipStream_t of that device (NULL = its null stream).  The call only
- *   enqueues two or three kernels there and returns; results are ready when the
+ *   enqueues one to three kernels there and returns; results are ready when the
  *   stream's work before the next synchronisation point has finished.
  * dev_x_pool, dev_y_pool: device float pools of pool_len elements each.
  * dev_jobs: device array of count set_vec_job; dev_results: device float
@@ -549,7 +549,8 @@ int set_run_vector_jobs(set_ctx *c, int template_id, const set_vec_job *jobs, ui
  * Work area: one static device array of about 4.8 MiB per GPU (descriptor
  * table, item partials, work counter), held from library load until the
  * process ends and shared by every call on that GPU.  Each call rewrites it
- * from its first kernel on (the counter included), so calls on one stream
+ * from its first kernel on (the counter included) unless all its jobs are short
+ * and take a single kernel without it, so calls on one stream
  * follow each other safely; calls that overlap on one GPU (different
  * streams, or different host threads without ordering) race on it and give
  * wrong results.  Errors: SET_EINVAL as above or for null pointers,

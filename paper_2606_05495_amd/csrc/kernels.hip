@@ -1403,6 +1403,12 @@ __device__ inline float tanh_f32(float z) {
   return fabsf(z) >= 0.8f ? big : small;
 }
 
+// Four elements of sum tanh(a*x + y).
+__device__ inline float vec_quad(float av, v4f_any xv, v4f_any yv) {
+  return (tanh_f32(fmaf(av, xv.x, yv.x)) + tanh_f32(fmaf(av, xv.y, yv.y))) +
+         (tanh_f32(fmaf(av, xv.z, yv.z)) + tanh_f32(fmaf(av, xv.w, yv.w)));
+}
+
 // Thread's share of sum tanh(a*x + y) over len elements, by a block of BLOCK
 // threads: thread j takes the 4-element groups j, j + BLOCK, ... in order, and
 // thread 0 the last len % 4 elements.  The order depends on len and BLOCK only.
@@ -1424,10 +1430,7 @@ __device__ __forceinline__ float vec_range_sum(const float* x, const float* y, f
     return *reinterpret_cast<const v4f_any __attribute__((address_space(1)))*>(base + o);
   };
   float acc = 0.f;
-  auto quad = [&](v4f_any xv, v4f_any yv) {
-    return (tanh_f32(fmaf(av, xv.x, yv.x)) + tanh_f32(fmaf(av, xv.y, yv.y))) +
-           (tanh_f32(fmaf(av, xv.z, yv.z)) + tanh_f32(fmaf(av, xv.w, yv.w)));
-  };
+  auto quad = [&](v4f_any xv, v4f_any yv) { return vec_quad(av, xv, yv); };
   uint64_t g = 0;
   for (; g + U * BLOCK <= ng; g += U * BLOCK) {
     v4f_any xv[U], yv[U];
@@ -1660,6 +1663,55 @@ __global__ __launch_bounds__(kBlock, 8) void k_vec_few_tiles(VecFewArgs a) {
   if (blockIdx.x >= T) return;
   vec_tiles<kBlock>(s_table, a.plan.count, T, blockIdx.x, a.x, a.y, a.partials,
                     [&](uint32_t t) { return gridDim.x < T - t ? t + gridDim.x : T; });
+}
+
+// Sum of one item of len elements by one wave, to the bit what the tile kernel's
+// block of 256 threads makes of it: lane l stands for its threads l, l + 64, l +
+// 128 and l + 192, whose loads go out together.
+__device__ __forceinline__ float vec_item_wave(const float* x, const float* y, float av, uint32_t len) {
+  static_assert(kBlock == 256, "four lanes' worth of threads");
+  const uint32_t lane = threadIdx.x & 63u, ng = len >> 2;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  for (uint32_t g0 = lane; g0 - lane < ng; g0 += kBlock) {
+    v4f_any xv[4], yv[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (g0 + 64 * w < ng) {
+        xv[w] = reinterpret_cast<const v4f_any*>(x)[g0 + 64 * w];
+        yv[w] = reinterpret_cast<const v4f_any*>(y)[g0 + 64 * w];
+      }
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (g0 + 64 * w < ng) s[w] += vec_quad(av, xv[w], yv[w]);
+  }
+  if ((len & 3u) && lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < (int)(len & 3u)) s[0] += tanh_f32(fmaf(av, x[4 * ng + k], y[4 * ng + k]));
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) s[w] = wave_total_f32(s[w]);
+  return tree_sum_f32<4>(s);
+}
+
+// A no-allocation call of short jobs in one launch: a block a job, a wave an item.
+// Nothing to plan, to find or to add up behind another kernel: the block reads its
+// own job, and wave 0 adds the items' sums in vec_job_total's order.
+__global__ __launch_bounds__(1024, 8) void k_vec_short_jobs(VecShortArgs a) {
+  __shared__ float s_item[kVecShortItems];
+  const VecBatchDesc d = vec_plan_job(a.plan, a.plan.jobs[blockIdx.x]);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  for (uint32_t k = wave; k < d.ntiles; k += blockDim.x >> 6) {
+    const uint32_t beg = k * d.tile_elems;
+    const float s = vec_item_wave(a.x + d.x_off + beg, a.y + d.y_off + beg, d.a,
+                                  d.n - beg < d.tile_elems ? d.n - beg : d.tile_elems);
+    if ((threadIdx.x & 63) == 0) s_item[k] = s;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const float s = wave_total_f32(threadIdx.x < d.ntiles ? 0.f + s_item[threadIdx.x] : 0.f);
+    if (threadIdx.x == 0) a.results[blockIdx.x] = d.n == 0 ? __builtin_nanf("") : s;
+  }
 }
 
 // Job j = wave: its tiles' partials in a fixed order.  Block 0 also rewinds the

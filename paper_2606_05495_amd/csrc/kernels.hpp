@@ -130,6 +130,13 @@ struct VecFewArgs {
   float* partials;
 };
 __global__ void k_vec_few_tiles(VecFewArgs a);
+struct VecShortArgs {
+  VecPlanArgs plan;
+  const float* x;
+  const float* y;
+  float* results;
+};
+__global__ void k_vec_short_jobs(VecShortArgs a);
 struct VecBatchFinalArgs {
   uint8_t* tab;
   const float* partials;

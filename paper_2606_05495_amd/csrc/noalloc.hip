@@ -9,7 +9,9 @@
 // work counter live in one static device array per GPU, whose address is
 // looked up once per device.
 //
-// Up to kBlock jobs take two launches on the caller's stream, a tile kernel whose
+// Short jobs (up to 32767 elements at the default item sizes) take one launch, a
+// block to a job (k_vec_short_jobs).
+// Other calls of up to kBlock jobs take two launches on the caller's stream, a tile kernel whose
 // blocks each plan the call in LDS and the totals; more take three:
 //   plan   (one block): validate each job, pick its item size, prefix-sum the
 //          tile counts into a descriptor table and rewind the work counter;
@@ -177,12 +179,14 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
   // Item size per bucket and the most items any job of length <= max_n needs.
   const int top = 63 - __builtin_clzll(max_n);
   uint64_t worst = 0, worst_units = 0;
+  uint32_t longest_item = 0;
   for (int b = 0; b < 64; ++b) {
     const uint32_t te = (tuning && tuning->tile_elems[b]) ? tuning->tile_elems[b] : vec_default_tile(b);
     if (b <= top) {
       if (te == 0 || te % 1024 != 0) return na_fail(SET_EINVAL, "tile_elems must be a positive multiple of 1024");
       const uint64_t nmax = b == 63 ? max_n : std::min<uint64_t>(max_n, (2ull << b) - 1);
       worst = std::max<uint64_t>(worst, (nmax + te - 1) / te);
+      longest_item = std::max(longest_item, te);
       worst_units = std::max<uint64_t>(worst_units, vec_units(nmax, te, kBlock));
     }
     pa.item_elems[b] = te;
@@ -212,7 +216,11 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     pa.split = count * worst_units <= kNaMaxItems;
     const uint64_t most_tiles = count * (pa.split ? worst_units : worst);
     pa.grid = grid ? grid : (uint32_t)std::min<uint64_t>(kNaGrid, most_tiles);
-    if (count <= (uint64_t)kBlock) {
+    const bool is_short = worst <= kVecShortItems && longest_item <= kVecShortItem && grid == 0;
+    if (is_short) {
+      VecShortArgs sa{pa, x, y, results};
+      hipLaunchKernelGGL(k_vec_short_jobs, dim3((unsigned)count), dim3(64 * (unsigned)worst), 0, stream, sa);
+    } else if (count <= (uint64_t)kBlock) {
       VecFewArgs fa{pa, x, y, partials};
       hipLaunchKernelGGL(k_vec_few_tiles, dim3(pa.grid), dim3(kBlock), 0, stream, fa);
     } else {
@@ -221,9 +229,11 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
       VecBatchArgs va{tab, x, y, partials, work, reinterpret_cast<DevSlotHdr*>(base + kNaHdrOff), js};
       hipLaunchKernelGGL(k_vec_batch_tiles<kBlock>, dim3(pa.grid), dim3(kBlock), 0, stream, va);
     }
-    NaTotalsArgs ta{tab, partials, results};
-    hipLaunchKernelGGL(k_vec_noalloc_totals, dim3((unsigned)((count + kVecFinalJobs - 1) / kVecFinalJobs)), dim3(kBlock),
-                       0, stream, ta);
+    if (!is_short) {
+      NaTotalsArgs ta{tab, partials, results};
+      hipLaunchKernelGGL(k_vec_noalloc_totals, dim3((unsigned)((count + kVecFinalJobs - 1) / kVecFinalJobs)),
+                         dim3(kBlock), 0, stream, ta);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) rc = na_fail(SET_EDEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
   }

@@ -75,6 +75,15 @@ SETRT_HD inline uint32_t vec_claim(uint64_t elems, uint32_t units, uint32_t grid
   return c < 1 ? 1 : c < share ? c : share;
 }
 constexpr int kVecUnitsPerItem = 4;  // most units of one work item
+// A no-allocation call whose jobs have at most this many work items, of at most
+// kVecShortItem elements each, takes a block to a job and a wave to an item.  In
+// us, planned / so: 1 to 256 jobs of up to 8192 12.5-14 / 10-11, 1000 22.9 / 12.6,
+// 2000 34.7 / 19.3, 2000 of up to 32767 61.6 / 42.6.  A wave takes a longer item in
+// rounds of one memory latency each, and the largest job sets the time: items of
+// 4096 took 300 jobs of up to 65535 21.2 / 22.8 (1000 46.5 / 41.1), of 8192 64 of up
+// to 131071 14.1 / 24.6.
+constexpr uint32_t kVecShortItems = 16;
+constexpr uint32_t kVecShortItem = 2048;
 constexpr int kVecFinalJobs = 4;     // jobs per block of the batch's last kernel: one wave each
 // Up to this many jobs to a batch, the last block of that kernel writes the results
 // to host memory, four to a thread; longer ones are left to the copy kernel's 32

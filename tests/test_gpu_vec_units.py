@@ -120,3 +120,34 @@ def test_job_search_and_claims(torch_gpu, pools, count, n_max, grid):
         j = jobs[i]
         S, E = oracle.saxpy_tanh_sum(x[j["x_off"]:j["x_off"] + j["n"]], y[j["y_off"]:j["y_off"] + j["n"]], j["a"])
         assert abs(float(got[i]) - S) <= oracle.vec_tolerance(S, E), (i, int(j["n"]), got[i], S)
+
+
+@pytest.mark.parametrize("n_max", [1, 3, 4, 257, 1023, 1024, 1025, 8192, 16383, 16384, 32767])
+@pytest.mark.parametrize("count", [1, 2, 255, 300, 3000])
+def test_short_jobs_match_the_general_path(torch_gpu, pools, count, n_max):
+    """A call of short jobs (a block to a job) gives the bits of the same call with
+    a grid, which takes the planned path: any alignment, lengths around items and
+    rows, rejected jobs, NaN and infinities, and items of 2048 elements."""
+    print("short jobs", count, n_max)
+    sys.stdout.flush()
+    rng = np.random.default_rng(count * 40000 + n_max)
+    xd, yd = pools[2].clone(), pools[3]
+    at = torch_gpu.from_numpy(rng.integers(0, POOL, 64)).cuda()
+    xd[at[:32]] = float("inf")
+    xd[at[32:48]] = float("nan")
+    edges = [v for v in (1, 2, 3, 4, 5, 255, 256, 1023, 1024, 1025, 2047, 2048, 2049, n_max - 1, n_max) if 1 <= v <= n_max]
+    n = np.where(rng.random(count) < 0.5, rng.choice(edges, count), rng.integers(1, n_max + 1, count))
+    jobs = _jobs(n, rng.integers(0, POOL - n), rng.integers(0, POOL - n), rng.uniform(0.5, 2, count).astype(np.float32))
+    bad = rng.random(count) < 0.05
+    jobs["n"][bad & (jobs["n"] % 2 == 0)] = 0
+    jobs["n"][bad & (jobs["n"] % 2 == 1)] = n_max + 1
+    jobs["x_off"][rng.random(count) < 0.02] = POOL
+    tuning = A.set_vec_tuning()
+    for b in range(64):
+        tuning.tile_elems[b] = 2048
+    for t in (None, tuning):
+        got = _noalloc(torch_gpu, xd, yd, jobs, n_max, t)
+        want = _noalloc(torch_gpu, xd, yd, jobs, n_max, t, grid=7)
+        same = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
+        assert same.all(), (n[~same], got[~same], want[~same])
+        assert np.isnan(got[jobs["n"] == 0]).all() and np.isnan(got[jobs["n"] > n_max]).all()
