@@ -192,7 +192,8 @@ enum set_pipeline {
 enum set_copy_mode {
     SET_COPY_KERNELS = 0, /* small-grid copy kernels, nodes of the job's graph, that pull the input from /
                              push the output to pinned host memory; host buffers must be 16-byte aligned.
-                             Small outputs (a histogram, sums, a batch's results; without SET_TF_DEBUG) have no
+                             Small outputs (a histogram, sums, a batch's results, a scan of max_n up to
+                             131072; without SET_TF_DEBUG) have no
                              copy: the last stage writes them to the host buffer, also in SET_COPY_ASYNC_IN.
                              Default: ROCm runs graph memcpy nodes as large-grid blit kernels that crowd
                              out the stage kernels */

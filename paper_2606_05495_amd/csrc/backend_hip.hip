@@ -934,11 +934,16 @@ class HipBackend : public Backend {
         sl.scan_r = ScanReduceArgs{(const int32_t*)(b + L.in), (int64_t*)sb, T, sc.hdr, JobScalars{}};
         sl.scan_r.js.n = t.max_n;
         sl.scan_s = ScanSpineArgs{(const int64_t*)sb, (int64_t*)(sb + q8), sc, t.max_n};
-        sl.scan_d = ScanDownArgs{(const int32_t*)(b + L.in), (const int64_t*)(sb + q8), (void*)(b + L.out + 64),
-                                 (t.flags & SET_TF_SCAN_LOW32) ? 1 : 0, t.max_n};
-        stage((const void*)&k_scan_reduce_i32, dim3(T), &sl.scan_r);
-        stage((const void*)&k_scan_spine_i64, dim3(1), &sl.scan_s);
-        stage((const void*)&k_scan_down_i32_i64, dim3(T), &sl.scan_d);
+        const int prefix = scan_prefix(t.max_n);
+        sl.scan_d = ScanDownArgs{(const int32_t*)(b + L.in), (const int64_t*)(prefix == SCAN_FROM_SPINE ? sb + q8 : sb),
+                                 (void*)payload, (t.flags & SET_TF_SCAN_LOW32) ? 1 : 0, sc, JobScalars{}};
+        sl.scan_d.js.n = t.max_n;
+        if (prefix != SCAN_FROM_INPUT) stage((const void*)&k_scan_reduce_i32, dim3(T), &sl.scan_r);
+        if (prefix == SCAN_FROM_SPINE) stage((const void*)&k_scan_spine_i64, dim3(1), &sl.scan_s);
+        stage(prefix == SCAN_FROM_INPUT  ? (const void*)&k_scan_down_i32_i64<SCAN_FROM_INPUT>
+              : prefix == SCAN_FROM_SUMS ? (const void*)&k_scan_down_i32_i64<SCAN_FROM_SUMS>
+                                         : (const void*)&k_scan_down_i32_i64<SCAN_FROM_SPINE>,
+              dim3(T), &sl.scan_d);
         break;
       }
     }
@@ -984,6 +989,10 @@ class HipBackend : public Backend {
         sl.gs.out_count = sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
         sl.gs.out_sum = sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
         break;
+      case SET_PIPE_SCAN_I32_I64:
+        sl.scan_d.sc.outh = h;
+        sl.scan_d.out = o + 64;
+        break;
       case SET_PIPE_SAXPY_BATCH_F32:
         sl.vbf.sc.outh = h;
         sl.vbf.results = reinterpret_cast<float*>(o + 64);
@@ -995,7 +1004,9 @@ class HipBackend : public Backend {
     }
   }
   // The last stage stores the completion word: nothing follows it in the graph.
-  bool flag_in_stage(const Pipe& p) const { return p.words && writes_out(p.t) && !poisons(p); }
+  bool flag_in_stage(const Pipe& p) const {
+    return p.words && writes_out(p.t) && !poisons(p) && p.t.pipeline != SET_PIPE_SCAN_I32_I64;
+  }
   static bool poisons(const Pipe& p) { return (p.t.flags & SET_TF_POISON) != 0; }
   static bool delays(const Pipe& p) { return p.t.stress_delay_us > 0; }
   static unsigned poison_blocks(const Pipe& p) {
@@ -1051,7 +1062,7 @@ class HipBackend : public Backend {
         if (js.n == 0) js.n = p.t.max_n;
         sl.scan_r.js = js;
         sl.scan_s.n = js.n;
-        sl.scan_d.n = js.n;
+        sl.scan_d.js = js;
         break;
       case SET_PIPE_SCAN_LIB_I32_I64:
         js.n = p.t.max_n;
@@ -1346,7 +1357,7 @@ class HipBackend : public Backend {
     hipKernelNodeParams kp = kparams(sl, 0);
     HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[0], &kp));
     if (p.t.pipeline == SET_PIPE_SCAN_I32_I64) {  // the spine and the downsweep carry n too
-      for (int i = 1; i <= 2; ++i) {
+      for (int i = 1; i < sl.nstages; ++i) {
         hipKernelNodeParams kd = kparams(sl, i);
         HIPCK(hipGraphExecKernelNodeSetParams(ex, cn.k[i], &kd));
       }

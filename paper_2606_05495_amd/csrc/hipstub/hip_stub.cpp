@@ -591,7 +591,14 @@ template void k_vec_batch_tiles<1024>(VecBatchArgs);
 void k_vec_batch_final(VecBatchFinalArgs a) { publish(a.sc); }
 void k_scan_reduce_i32(ScanReduceArgs a) { stamp(a.hdr, a.js); }
 void k_scan_spine_i64(ScanSpineArgs a) { publish(a.sc); }
-void k_scan_down_i32_i64(ScanDownArgs) {}
+template <int PREFIX>
+void k_scan_down_i32_i64(ScanDownArgs a) {
+  if (PREFIX == SCAN_FROM_INPUT) stamp(a.sc.hdr, a.js);
+  if (PREFIX != SCAN_FROM_SPINE) publish(a.sc);
+}
+template void k_scan_down_i32_i64<SCAN_FROM_INPUT>(ScanDownArgs);
+template void k_scan_down_i32_i64<SCAN_FROM_SUMS>(ScanDownArgs);
+template void k_scan_down_i32_i64<SCAN_FROM_SPINE>(ScanDownArgs);
 hipError_t lib_scan(void*, size_t& ws_bytes, const int32_t*, int64_t*, size_t, hipStream_t) {
   ws_bytes = 256;
   return hipErrorNotSupported;
@@ -651,7 +658,9 @@ struct Register {
     register_kernel(&k_vec_batch_final);
     register_kernel(&k_scan_reduce_i32);
     register_kernel(&k_scan_spine_i64);
-    register_kernel(&k_scan_down_i32_i64);
+    register_kernel(&k_scan_down_i32_i64<SCAN_FROM_INPUT>);
+    register_kernel(&k_scan_down_i32_i64<SCAN_FROM_SUMS>);
+    register_kernel(&k_scan_down_i32_i64<SCAN_FROM_SPINE>);
   }
 } g_register;
 }  // namespace

@@ -149,13 +149,15 @@ inline bool one_kernel_image(const set_job_template& t) {
   return t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 && !(t.flags & SET_TF_DEBUG) &&
          gauss_sobel_in_one((int)t.height, (int)t.width);
 }
-// Templates whose last stage writes the job's output to host memory itself, from
-// the one block that has all of it: small outputs without intermediate images, of copy modes
-// whose output copy is a kernel.
+// Templates whose last stage writes the job's output to host memory itself: small
+// outputs without intermediate images, of copy modes whose output copy is a kernel.
+// The block that has all of it does (and stores the completion word), or, for
+// one-kernel scans, every block its part.
 inline bool writes_out(const set_job_template& t) {
   return t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG) &&
          (t.pipeline == SET_PIPE_BOX_HIST_U8 || t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 ||
           t.pipeline == SET_PIPE_SAXPY_TANH_SUM_F32 ||
+          (t.pipeline == SET_PIPE_SCAN_I32_I64 && scan_prefix(t.max_n) == SCAN_FROM_INPUT) ||
           (t.pipeline == SET_PIPE_SAXPY_BATCH_F32 && t.batch_max <= kVecFinishJobs));
 }
 // Static per-job sizes of a template (in/out bytes for a job with length n).

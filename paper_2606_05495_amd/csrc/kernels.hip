@@ -1747,8 +1747,10 @@ __global__ __launch_bounds__(kBlock) void k_vec_batch_final(VecBatchFinalArgs a)
 
 // ------------------------------------------------------------------ inclusive scan int32 -> int64
 // Reduce-then-scan: tile sums, an exclusive scan of the tile sums in one
-// block, then each tile scans itself from its offset.  Integer addition is
-// exact, so any order gives the same sums; no block waits on another.
+// block, then each tile scans itself from its offset.  Up to 2^21 elements a
+// tile's block adds up the sums before its own instead, and up to 2^17 the input
+// before its own, in one kernel: short scans are launches and latency.  Integer
+// addition is exact, so any order gives the same sums; no block waits on another.
 
 // Loads the kScanItems values thread tid owns in tile t (zeros past n).
 __device__ inline void scan_load(const int32_t* in, uint64_t n, unsigned t, int tid, int64_t v[kScanItems]) {
@@ -1861,12 +1863,22 @@ __global__ __launch_bounds__(kBlock) void k_scan_spine_i64(ScanSpineArgs a) {
 // elements per thread), then pass through LDS so that each store instruction
 // of a wave writes one contiguous 1 KiB run: a thread's own 64-byte run would
 // make every store instruction touch 32 lines a quarter each.
+template <int PREFIX>
 __global__ __launch_bounds__(kBlock) void k_scan_down_i32_i64(ScanDownArgs a) {
   constexpr int kPitch = kScanItems + 2;  // LDS row of a thread (padding spreads the banks, keeps 16-byte alignment)
   __shared__ int64_t s_wave[4];
+  __shared__ int64_t s_before[4];
   __shared__ __align__(16) int64_t s_out[kBlock * kPitch];
-  const uint64_t n = a.n;
+  const uint64_t n = a.js.n;
   const unsigned t = blockIdx.x;
+  if (PREFIX != SCAN_FROM_SPINE && t == 0 && threadIdx.x == 0) {
+    if (PREFIX == SCAN_FROM_INPUT) {
+      write_slot_hdr(a.sc.hdr, a.js);
+      store_out(a.sc, load_out(a.sc, a.js), true);
+    } else {
+      publish_out(a.sc, true);
+    }
+  }
   if ((uint64_t)t * kScanTile >= n) return;
   // The thread's 8 values as two 16-byte loads with no branch around them,
   // then the tile's prefix, held at this point by the empty asm statement
@@ -1881,15 +1893,45 @@ __global__ __launch_bounds__(kBlock) void k_scan_down_i32_i64(ScanDownArgs a) {
   const uint64_t ld = base < last ? base : last;
   const int4 q0 = *reinterpret_cast<const int4*>(a.in + ld);
   const int4 q1 = *reinterpret_cast<const int4*>(a.in + ld + 4);
-  const int64_t tile_off = a.tile_excl[t];
-  asm volatile("" ::"s"(tile_off) : "memory");
+  int64_t tile_off = 0, before = 0;  // the block's, or a thread's share of it
+  if constexpr (PREFIX == SCAN_FROM_SPINE) {
+    tile_off = a.tiles[t];
+    asm volatile("" ::"s"(tile_off) : "memory");
+  } else if constexpr (PREFIX == SCAN_FROM_SUMS) {
+    int64_t w[kScanSumTiles / kBlock];
+#pragma unroll
+    for (unsigned k = 0; k < kScanSumTiles / kBlock; ++k) {
+      const unsigned i = threadIdx.x + k * kBlock;
+      w[k] = a.tiles[i < t ? i : 0];
+    }
+#pragma unroll
+    for (unsigned k = 0; k < kScanSumTiles / kBlock; ++k) before += threadIdx.x + k * kBlock < t ? w[k] : 0;
+  } else {
+    // two 16-byte words of each tile to a thread, 16 words going out together
+    const unsigned words = t * (kScanTile / 4 / kBlock);
+    for (unsigned k0 = 0; k0 < words; k0 += 16) {
+      int4 w[16];
+#pragma unroll
+      for (unsigned k = 0; k < 16; ++k)
+        w[k] = reinterpret_cast<const int4*>(a.in)[k0 + k < words ? threadIdx.x + (k0 + k) * kBlock : threadIdx.x & 1];
+#pragma unroll
+      for (unsigned k = 0; k < 16; ++k)
+        before += k0 + k < words ? ((int64_t)w[k].x + w[k].y) + ((int64_t)w[k].z + w[k].w) : 0;
+    }
+  }
   int64_t v[kScanItems] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? v[k] : 0;
 #pragma unroll
   for (int k = 1; k < kScanItems; ++k) v[k] += v[k - 1];
+  if constexpr (PREFIX != SCAN_FROM_SPINE) {
+    before = wave_inclusive_i64(before);
+    if ((threadIdx.x & 63) == 63) s_before[threadIdx.x >> 6] = before;
+  }
   int64_t total;
-  const int64_t off0 = tile_off + block_exclusive_i64(v[kScanItems - 1], s_wave, &total);
+  int64_t off0 = block_exclusive_i64(v[kScanItems - 1], s_wave, &total);  // its barriers are s_before's too
+  if constexpr (PREFIX != SCAN_FROM_SPINE) tile_off = (s_before[0] + s_before[1]) + (s_before[2] + s_before[3]);
+  off0 += tile_off;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) s_out[threadIdx.x * kPitch + k] = off0 + v[k];
   __syncthreads();
@@ -1921,5 +1963,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_down_i32_i64(ScanDownArgs a) {
     }
   }
 }
+template __global__ void k_scan_down_i32_i64<SCAN_FROM_INPUT>(ScanDownArgs a);
+template __global__ void k_scan_down_i32_i64<SCAN_FROM_SUMS>(ScanDownArgs a);
+template __global__ void k_scan_down_i32_i64<SCAN_FROM_SPINE>(ScanDownArgs a);
 
 }  // namespace setrt

@@ -146,8 +146,9 @@ struct VecBatchFinalArgs {
   uint32_t* arrivals;  // where the last block writes the output (arrival_bytes(grid)), or null
   uint32_t n;          // results it writes
 };
-// Scan as reduce -> spine -> downsweep; all three are launched with the grid
-// of the template's largest n, so a job of any length needs no grid update.
+// Scan as reduce -> spine -> downsweep, or without the first one or two where the
+// downsweep's blocks add up what lies before them (scan_prefix); launched with the
+// grid of the template's largest n, so a job of any length needs no grid update.
 // The reduce and the downsweep take the job's n in their argument blocks; the
 // one-block spine reads it from the slot header.
 struct ScanReduceArgs {
@@ -168,10 +169,11 @@ struct ScanSpineArgs {
 // header first: one memory round trip instead of two.
 struct ScanDownArgs {
   const int32_t* in;
-  const int64_t* tile_excl;
+  const int64_t* tiles;  // the spine's tile_excl, or the reduce's tile_sum
   void* out;           // int64[n], or uint32[n] low words
   int low32;
-  uint64_t n;          // the job's length
+  SlotConst sc;        // without the spine, block 0 publishes the header
+  JobScalars js;       // n; without the reduce, block 0 writes them to the slot
 };
 
 // Host<->device copy as a kernel: a small grid of 16-byte loads/stores that
@@ -368,6 +370,7 @@ __global__ void k_vec_batch_tiles(VecBatchArgs a);
 __global__ void k_vec_batch_final(VecBatchFinalArgs a);
 __global__ void k_scan_reduce_i32(ScanReduceArgs a);
 __global__ void k_scan_spine_i64(ScanSpineArgs a);
+template <int PREFIX>
 __global__ void k_scan_down_i32_i64(ScanDownArgs a);
 
 }  // namespace setrt

@@ -235,6 +235,21 @@ SETRT_HD inline uint64_t vec_chunk(uint64_t n, unsigned g) {
   return (c + q - 1) / q * q;
 }
 SETRT_HD inline unsigned scan_tiles(uint64_t n) { return (unsigned)((n + kScanTile - 1) / kScanTile); }
+// Where a downsweep block has the sum of the tiles before its own from, by the
+// template's largest length: it adds up to kScanRawTiles - 1 tiles of the input
+// itself (one kernel a job, which also writes the output to host memory), up to
+// kScanSumTiles - 1 tile sums (two kernels), or reads the spine's prefix (three).
+// 32 jobs, us, three kernels and a copy / two / one: 1000 elements 258 / 227 / 202,
+// 16000 341 / 330 / 282, 65000 - / 546 / 488, 100000 842 / 813 / 717, 130000 - / 958 /
+// 860; from there the input is read too often (200000 by one kernel: one job 98 /
+// 104), and output written by the downsweep is held up in its many blocks (2^21,
+// one job 540 / 595, where two kernels and a copy take what three took).
+constexpr unsigned kScanRawTiles = 64, kScanSumTiles = 1024;
+enum { SCAN_FROM_INPUT, SCAN_FROM_SUMS, SCAN_FROM_SPINE };
+inline int scan_prefix(uint64_t max_n) {
+  const unsigned t = scan_tiles(max_n);
+  return t <= kScanRawTiles ? SCAN_FROM_INPUT : t <= kScanSumTiles ? SCAN_FROM_SUMS : SCAN_FROM_SPINE;
+}
 
 // Byte layout of one buffer slot of a template (offsets from the slot base,
 // all 256-byte aligned).  In debug templates the intermediate images live
