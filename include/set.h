@@ -183,8 +183,8 @@ enum set_pipeline {
      *   T' = T + 0.5*P + 0.1*(N + S - 2T) + 0.1*(W + E - 2T) + (300 - T)/640
      * with N, S, W, E the four neighbours and a neighbour outside the grid
      * taken as the cell itself (no heat crosses the border).  The header is
-     * published by the output copy kernel, or by a kernel ahead of a memcpy
-     * node.  out: set_out_header + T_K (float32, row-major). */
+     * published by the output copy kernel, by the last step of a small grid that
+     * writes its output itself, or by a kernel ahead of a memcpy node.  out: set_out_header + T_K (float32, row-major). */
     SET_PIPE_HOTSPOT_F32 = 6
 };
 
@@ -192,8 +192,8 @@ enum set_pipeline {
 enum set_copy_mode {
     SET_COPY_KERNELS = 0, /* small-grid copy kernels, nodes of the job's graph, that pull the input from /
                              push the output to pinned host memory; host buffers must be 16-byte aligned.
-                             Small outputs (a histogram, sums, a batch's results, a scan of max_n up to
-                             131072; without SET_TF_DEBUG) have no
+                             Small outputs (a histogram, sums, a batch's results, a scan of max_n or a
+                             thermal grid of up to 131072; without SET_TF_DEBUG) have no
                              copy: the last stage writes them to the host buffer, also in SET_COPY_ASYNC_IN.
                              Default: ROCm runs graph memcpy nodes as large-grid blit kernels that crowd
                              out the stage kernels */

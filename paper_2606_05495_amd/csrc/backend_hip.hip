@@ -904,9 +904,9 @@ class HipBackend : public Backend {
         const int L = hotspot_launches(h, w, K);
         for (int k = 0; k < L; ++k) {
           const float* src = (k == 0) ? (const float*)(b + p.L.in) : sl.hot[k - 1].tout;
-          float* dst = (k == L - 1) ? (float*)(b + p.L.out + 64) : (float*)(b + ((k % 2 == 0) ? p.L.b1 : p.L.b2));
+          float* dst = (k == L - 1) ? (float*)payload : (float*)(b + ((k % 2 == 0) ? p.L.b1 : p.L.b2));
           const int n = hotspot_steps(h, w, K, k), hr = hotspot_band_rows(h, w);
-          sl.hot[k] = HotspotArgs{src, P, dst, h, w, k == 0 ? 1 : 0, n, sc.hdr, JobScalars{}};
+          sl.hot[k] = HotspotArgs{src, P, dst, h, w, k == 0 ? 1 : 0, wo && k == L - 1 ? 1 : 0, n, sc, JobScalars{}};
           if (n > 1)
             stage(mks[hotspot_halo(n) - 1], to_dim3(hotspot_steps_grid(h, w, hotspot_halo(n))), &sl.hot[k]);
           else if (hr)
@@ -915,7 +915,7 @@ class HipBackend : public Backend {
           else
             stage(hk, to_dim3(hotspot_grid(h, w)), &sl.hot[k]);
         }
-        if (!publishes_in_copy(t)) {
+        if (!wo && !publishes_in_copy(t)) {
           sl.je = JobEndArgs{sc};
           stage((const void*)&k_job_end, dim3(1), &sl.je);
         }
@@ -989,6 +989,10 @@ class HipBackend : public Backend {
         sl.gs.out_count = sl.sobelf.out_count = reinterpret_cast<uint32_t*>(o + 64);
         sl.gs.out_sum = sl.sobelf.out_sum = reinterpret_cast<float*>(o + 68);
         break;
+      case SET_PIPE_HOTSPOT_F32:
+        sl.hot[sl.nstages - 1].sc.outh = h;
+        sl.hot[sl.nstages - 1].tout = reinterpret_cast<float*>(o + 64);
+        break;
       case SET_PIPE_SCAN_I32_I64:
         sl.scan_d.sc.outh = h;
         sl.scan_d.out = o + 64;
@@ -1005,7 +1009,8 @@ class HipBackend : public Backend {
   }
   // The last stage stores the completion word: nothing follows it in the graph.
   bool flag_in_stage(const Pipe& p) const {
-    return p.words && writes_out(p.t) && !poisons(p) && p.t.pipeline != SET_PIPE_SCAN_I32_I64;
+    return p.words && writes_out(p.t) && !poisons(p) && p.t.pipeline != SET_PIPE_SCAN_I32_I64 &&
+           p.t.pipeline != SET_PIPE_HOTSPOT_F32;
   }
   static bool poisons(const Pipe& p) { return (p.t.flags & SET_TF_POISON) != 0; }
   static bool delays(const Pipe& p) { return p.t.stress_delay_us > 0; }
@@ -1070,6 +1075,7 @@ class HipBackend : public Backend {
         break;
       case SET_PIPE_HOTSPOT_F32:
         sl.hot[0].js = js;
+        if (writes_out(p.t)) sl.hot[sl.nstages - 1].js = js;
         break;
       case SET_PIPE_SAXPY_BATCH_F32:
         sl.vb.js = js;

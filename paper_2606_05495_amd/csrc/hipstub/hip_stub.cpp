@@ -517,28 +517,32 @@ void k_stress_delay(DelayArgs a) {  // the stand-in clock runs at 100 MHz
 }
 void k_job_begin(JobBeginArgs a) { stamp(a.hdr, a.js); }
 void k_job_end(JobEndArgs a) { publish(a.sc); }
+void hotspot_headers(const HotspotArgs& a) {
+  if (a.first) stamp(a.sc.hdr, a.js);
+  if (a.publish) publish(a.sc);
+}
 template <bool FULL>
 void k_hotspot_win_f32(HotspotArgs a) {
-  if (a.first) stamp(a.hdr, a.js);
+  hotspot_headers(a);
 }
 template void k_hotspot_win_f32<true>(HotspotArgs);
 template void k_hotspot_win_f32<false>(HotspotArgs);
 template <int R>
 void k_hotspot_band_f32(HotspotArgs a) {
-  if (a.first) stamp(a.hdr, a.js);
+  hotspot_headers(a);
 }
 template void k_hotspot_band_f32<8>(HotspotArgs);
 template void k_hotspot_band_f32<16>(HotspotArgs);
 template <int HALO>
 void k_hotspot_steps_f32(HotspotArgs a) {
-  if (a.first) stamp(a.hdr, a.js);
+  hotspot_headers(a);
 }
 template void k_hotspot_steps_f32<1>(HotspotArgs);
 template void k_hotspot_steps_f32<2>(HotspotArgs);
 template void k_hotspot_steps_f32<3>(HotspotArgs);
 template void k_hotspot_steps_f32<4>(HotspotArgs);
 void k_hotspot_f32(HotspotArgs a) {
-  if (a.first) stamp(a.hdr, a.js);
+  hotspot_headers(a);
 }
 void k_box3_u8_u16(BoxArgs a) { stamp(a.hdr, a.js); }
 void k_div9_u16_u8(Div9Args) {}

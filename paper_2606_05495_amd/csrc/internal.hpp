@@ -138,11 +138,6 @@ struct TemplateSizes {
   char stage_names[kMaxStages][32];
 };
 
-// Templates whose output copy kernel publishes the header: no stage of theirs
-// runs in one block behind the others.
-inline bool publishes_in_copy(const set_job_template& t) {
-  return t.copy_mode != SET_COPY_NODES && t.pipeline == SET_PIPE_HOTSPOT_F32;
-}
 // Image templates that take the Gaussian and Sobel in one kernel, whose last block
 // publishes the output.
 inline bool one_kernel_image(const set_job_template& t) {
@@ -152,13 +147,19 @@ inline bool one_kernel_image(const set_job_template& t) {
 // Templates whose last stage writes the job's output to host memory itself: small
 // outputs without intermediate images, of copy modes whose output copy is a kernel.
 // The block that has all of it does (and stores the completion word), or, for
-// one-kernel scans, every block its part.
+// one-kernel scans and thermal grids, every block its part.
 inline bool writes_out(const set_job_template& t) {
   return t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG) &&
          (t.pipeline == SET_PIPE_BOX_HIST_U8 || t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 ||
           t.pipeline == SET_PIPE_SAXPY_TANH_SUM_F32 ||
           (t.pipeline == SET_PIPE_SCAN_I32_I64 && scan_prefix(t.max_n) == SCAN_FROM_INPUT) ||
+          (t.pipeline == SET_PIPE_HOTSPOT_F32 && (int64_t)t.width * t.height <= kHotHostCells) ||
           (t.pipeline == SET_PIPE_SAXPY_BATCH_F32 && t.batch_max <= kVecFinishJobs));
+}
+// Templates whose output copy kernel publishes the header: no stage of theirs
+// runs in one block behind the others.
+inline bool publishes_in_copy(const set_job_template& t) {
+  return t.copy_mode != SET_COPY_NODES && t.pipeline == SET_PIPE_HOTSPOT_F32 && !writes_out(t);
 }
 // Static per-job sizes of a template (in/out bytes for a job with length n).
 uint64_t pipeline_in_bytes(const set_job_template& t, uint64_t n);

@@ -1061,6 +1061,13 @@ __device__ inline float step(float t, float q, float n, float s, float w, float 
 }
 }  // namespace hotspot
 
+// One thread of a launch: the job's first writes its scalars into the slot, one
+// that writes the output to host memory publishes its header there.
+__device__ inline void hotspot_headers(const HotspotArgs& a) {
+  if (a.first) write_slot_hdr(a.sc.hdr, a.js);
+  if (a.publish) store_out(a.sc, load_out(a.sc, a.js), true);
+}
+
 // Register window as for the image stages: a lane owns 4 columns, a wave 256
 // columns x kHotWinRows rows with its rows of T (plus one above and below)
 // and of P loaded before the first result.
@@ -1069,7 +1076,7 @@ __global__ __launch_bounds__(kBlock) void k_hotspot_win_f32(HotspotArgs a) {
   constexpr int R = kHotWinRows;
   unsigned bx, by;
   xcd_tile(bx, by);
-  if (a.first && bx == 0 && by == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  if (bx == 0 && by == 0 && threadIdx.x == 0) hotspot_headers(a);
   const int w = a.w, h = a.h, wm = w - 1, hm = h - 1;
   const WinLane<FULL> L(w, bx, by, R);
   const int xw = (int)bx * kWinCols;
@@ -1121,7 +1128,7 @@ __global__ __launch_bounds__(kBandCols / 4) void k_hotspot_band_f32(HotspotArgs 
   constexpr int nw = kBandCols / kWinCols;
   unsigned bx, band;
   xcd_tile(bx, band);  // grid (column blocks, bands)
-  if (a.first && bx == 0 && band == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  if (bx == 0 && band == 0 && threadIdx.x == 0) hotspot_headers(a);
   __shared__ float lo[nw + 2][R], hi[nw + 2][R];
   const int w = a.w, h = a.h, hm = h - 1;
   const int lane = threadIdx.x & 63;
@@ -1232,7 +1239,7 @@ __global__ __launch_bounds__(kBlock) void k_hotspot_steps_f32(HotspotArgs a) {
   static_assert(G * R == kHotTile && 16 * 4 == kHotTile, "square tile");
   unsigned bx, by;
   xcd_tile(bx, by);
-  if (a.first && bx == 0 && by == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  if (bx == 0 && by == 0 && threadIdx.x == 0) hotspot_headers(a);
   __shared__ v4f_t s_top[2][G][16], s_bottom[2][G][16];
   const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int x = (int)bx * U - S + 4 * lane, y = (int)by * U - S + R * grp;
@@ -1307,7 +1314,7 @@ template __global__ void k_hotspot_steps_f32<4>(HotspotArgs a);
 
 // Widths that are not a multiple of 4: one cell per thread.
 __global__ __launch_bounds__(kBlock) void k_hotspot_f32(HotspotArgs a) {
-  if (a.first && blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
+  if (blockIdx.x == 0 && threadIdx.x == 0) hotspot_headers(a);
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= (int64_t)a.h * a.w) return;
   const int y = (int)(i / a.w), x = (int)(i - (int64_t)y * a.w);

@@ -256,9 +256,10 @@ struct HotspotArgs {
   float* tout;
   int h, w;
   int first;
+  int publish;         // tout is the job's output in host memory
   int steps;
-  DevSlotHdr* hdr;
-  JobScalars js;
+  SlotConst sc;
+  JobScalars js;       // in the first and the publishing launch
 };
 template <int HALO>
 __global__ void k_hotspot_steps_f32(HotspotArgs a);

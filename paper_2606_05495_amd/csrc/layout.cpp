@@ -332,7 +332,7 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
       // each launch (of one or more steps) reads T and P and writes T'
       for (int k = 0; k < hotspot_launches((int)t.height, (int)t.width, (int)t.max_n); ++k)
         stage("hotspot_step_f32", 12 * npix);
-      if (!publishes_in_copy(t)) stage("job_end", 64 + 64);
+      if (!writes_out(t) && !publishes_in_copy(t)) stage("job_end", 64 + 64);
       break;
     case SET_PIPE_SCAN_LIB_I32_I64:
       stage("job_begin", 64);

@@ -206,6 +206,11 @@ inline Grid3 hotspot_grid(int h, int w) {
 // 1500 x 2000, K = 32: 947 / 803 / 794 / 841; 4096^2, K = 16: 4217 / 3837 /
 // 3825 / 3971.
 constexpr int kHotTile = 64;
+// Up to this many cells a job's last launch writes the grid to host memory itself.
+// Jobs, us, with an output copy / so: 64 of 32^2 402-465 / 354-396, one 47-51 / 40,
+// 64 of 128^2 658 / 601, of 256^2 891 / 871, 32 of 333^2 746 / 731; from 512^2 up
+// the link sets the time either way, and its stores hold the launch's blocks.
+constexpr int64_t kHotHostCells = 1 << 17;
 inline int hotspot_steps_max(int h, int w) { return (int64_t)h * w <= (int64_t)512 * 512 ? 16 : 8; }
 inline int hotspot_launches(int h, int w, int K) {
   const int m = hotspot_steps_max(h, w);

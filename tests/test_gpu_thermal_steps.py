@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_2606_05495_amd import _abi as A
 from paper_2606_05495_amd import synth
 from paper_2606_05495_amd.runtime import Context, pinned
 
@@ -71,3 +72,45 @@ def test_rounding_is_below_the_formula_as_it_stands(torch_gpu, case):
     ref = oracle.hotspot(t0, p, steps)
     rms = lambda v: float(np.sqrt(np.mean((v.astype(np.float64) - ref) ** 2)))
     assert t.dtype == np.float32 and rms(got) < rms(t)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (9, 260), (362, 362), (363, 362), (64, 2048), (64, 2052)])
+def test_output_in_every_way(torch_gpu, shape):
+    """Grids on both sides of the size up to which the last launch writes the
+    output to host memory: the same bits, with their own header, in every way a
+    job is launched, several jobs through each slot."""
+    h, w = shape
+    t0, p = synth.hotspot_input(9, h * 1000 + w, h, w)
+    ib, ob = 8 * h * w, 64 + 4 * h * w
+    tin, nin = pinned(ib)
+    nin[:ib].view(np.float32)[:] = np.concatenate([t0.ravel(), p.ravel()])
+    ways = {"direct": (dict(mode="set", callback="event_poll"), dict(copy="async_in")),
+            "words, poisoned": (dict(mode="set", callback="host_flag"), dict(flags=A.SET_TF_POISON)),
+            "captured": (dict(mode="set", callback="host_flag"), dict(flags=A.SET_TF_CAPTURE)),
+            "memcpy nodes": (dict(mode="set", callback="event_poll"), dict(copy="nodes")),
+            "batch": (dict(mode="batch", batch_size=4), {})}
+    stride = -(-ob // 64) * 64
+    for steps in (1, 16, 17):
+        ref = oracle.hotspot(t0, p, steps)
+        bits = None
+        for way, (kw, t) in ways.items():
+            print("thermal output", shape, steps, way)
+            sys.stdout.flush()
+            tout, nout = pinned(stride * 6)
+            nout[:] = 0xEE
+            with Context(workers=2, slots=2, **kw) as ctx:
+                tid = ctx.define("hotspot", width=w, height=h, max_n=steps, **t)
+                arr = ctx.job_array(6)
+                arr["host_in"], arr["in_bytes"], arr["out_bytes"] = tin.data_ptr(), ib, ob
+                arr["host_out"] = tout.data_ptr() + np.arange(6, dtype=np.uint64) * stride
+                first = ctx.submit_many(tid, arr)
+                ctx.drain()
+            for i in range(6):
+                o = nout[i * stride:i * stride + ob]
+                hd = o[:64].view(A.OUT_HEADER_DTYPE)[0]
+                assert hd["job_id"] == first + i and hd["magic"] == A.SET_OUT_MAGIC and hd["canary_ok"] == 1
+                if bits is None:
+                    bits = o[64:].tobytes()
+                    got = o[64:].view(np.float32).reshape(h, w)
+                    assert np.max(np.abs(got - ref)) <= oracle.hotspot_tolerance(ref, steps)
+                assert o[64:].tobytes() == bits, (way, i)
