@@ -419,7 +419,8 @@ int set_template_footprint(const set_config *cfg, const set_job_template *t,
  * batch graph is built instead.  In SET mode no graph is built for a template
  * whose jobs are at most six launches, copy less than 1 MiB in all and have
  * their output written by a kernel, unless it asks for a captured graph
- * (SET_TF_CAPTURE, library calls): its kernels are launched directly.  *template_id receives the id (0, 1, ...).
+ * (SET_TF_CAPTURE, library calls) or is a vector batch with SET_COPY_ASYNC_IN:
+ * its kernels are launched directly.  *template_id receives the id (0, 1, ...).
  * Must be called before any submit of that template. */
 int set_template_define(set_ctx *c, const set_job_template *t, int *template_id);
 
