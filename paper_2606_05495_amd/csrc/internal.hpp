@@ -75,11 +75,17 @@ static_assert(sizeof(set_job_template) == 96, "set_job_template layout");
 // Each job carries its own work-item size, so one batch may mix size buckets
 // while every job's result still depends only on (n, its item size).  A tile is
 // what a block takes: a work item, or one of its units (vec_unit_elems).
+// `claim`, `unit_elems` and `per_item` are read only where `planned` says that the
+// library built the table: in one submitted by hand they are padding, every tile is a
+// whole work item and is claimed by itself.
+constexpr uint64_t kVecPlanned = 0x73656C6974636576ull;
 struct VecBatchHdr {
   uint32_t count;        // jobs in the batch
   uint32_t total_tiles;  // tiles in the batch
   uint32_t claim;        // tiles a block claims at a time (vec_claim)
-  uint32_t pad[13];
+  uint32_t pad0;
+  uint64_t planned;      // kVecPlanned
+  uint32_t pad[10];
 };
 struct VecBatchDesc {
   uint64_t x_off, y_off;

@@ -1553,9 +1553,10 @@ __device__ inline uint32_t vec_find_job(const VecBatchDesc* D, uint32_t count, u
 // next tile's job and leaves its descriptor in LDS; one barrier ends a tile (the
 // LDS words are double, so the next tile's writes cannot meet this one's
 // reads).  A tile's partial depends on its job and BLOCK only, so which block
-// takes it changes no result.
+// takes it changes no result.  A table that the library did not plan may hold
+// items past their job's end, which sum to nothing.
 template <int BLOCK, class Next>
-__device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count, uint32_t T, uint32_t first,
+__device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count, uint32_t T, uint32_t first, bool planned,
                                           const float* px, const float* py, float* partials, Next next) {
   constexpr int W = BLOCK / 64;
   __shared__ float s_sum[2][kVecUnitsPerItem][W];
@@ -1582,9 +1583,10 @@ __device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count,
     const VecBatchDesc& d = s_desc[cur];
     auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
     auto scalar64 = [&](uint64_t v) { return (uint64_t)scalar((uint32_t)(v >> 32)) << 32 | scalar((uint32_t)v); };
-    const uint32_t te = scalar(d.tile_elems), ue = scalar(d.unit_elems), n = scalar(d.n);
+    const uint32_t te = scalar(d.tile_elems), n = scalar(d.n);
+    const uint32_t ue = planned ? scalar(d.unit_elems) : vec_hand_unit(te, BLOCK);
     const uint64_t beg = (uint64_t)(t - scalar(d.tile_start)) * te;
-    const uint64_t len = beg + te < n ? te : n - beg;
+    const uint64_t len = beg + te < n ? te : beg < n ? n - beg : 0;
     const float av = __int_as_float((int)scalar((uint32_t)__float_as_int(d.a)));
     const float* x = px + scalar64(d.x_off) + beg;
     const float* y = py + scalar64(d.y_off) + beg;
@@ -1596,7 +1598,7 @@ __device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count,
     if (wave == 0) publish(scalar(after), cur ^ 1);
     __syncthreads();
     if (threadIdx.x == 0) {
-      float s = tree_sum_f32<W>(s_sum[cur][0]);
+      float s = units > 0 ? tree_sum_f32<W>(s_sum[cur][0]) : 0.f;
       for (int u = 1; u < units; ++u) s += tree_sum_f32<W>(s_sum[cur][u]);
       partials[t] = s;
     }
@@ -1614,11 +1616,12 @@ __global__ __launch_bounds__(BLOCK, 8) void k_vec_batch_tiles(VecBatchArgs a) {
   if (blockIdx.x == 0 && threadIdx.x == 0) write_slot_hdr(a.hdr, a.js);
   const VecBatchHdr* H = reinterpret_cast<const VecBatchHdr*>(a.tab);
   const VecBatchDesc* D = reinterpret_cast<const VecBatchDesc*>(a.tab + sizeof(VecBatchHdr));
-  const uint32_t T = H->total_tiles, run = H->claim;
+  const bool planned = H->planned == kVecPlanned;
+  const uint32_t T = H->total_tiles, run = planned ? H->claim : 1u;
   const uint64_t first = (uint64_t)blockIdx.x * run, dealt = (uint64_t)gridDim.x * run;
   if (first >= T) return;
   uint32_t left = run;  // tiles of the run still to do, the current one included
-  vec_tiles<BLOCK>(D, H->count, T, (uint32_t)first, a.x, a.y, a.partials, [&](uint32_t t) {
+  vec_tiles<BLOCK>(D, H->count, T, (uint32_t)first, planned, a.x, a.y, a.partials, [&](uint32_t t) {
     if (--left != 0) return t + 1;
     left = run;
     uint32_t after = T;
@@ -1668,7 +1671,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_vec_few_tiles(VecFewArgs a) {
   }
   __syncthreads();
   if (blockIdx.x >= T) return;
-  vec_tiles<kBlock>(s_table, a.plan.count, T, blockIdx.x, a.x, a.y, a.partials,
+  vec_tiles<kBlock>(s_table, a.plan.count, T, blockIdx.x, true, a.x, a.y, a.partials,
                     [&](uint32_t t) { return gridDim.x < T - t ? t + gridDim.x : T; });
 }
 
@@ -1734,7 +1737,8 @@ __global__ __launch_bounds__(kBlock) void k_vec_batch_final(VecBatchFinalArgs a)
   OutWords w{};
   if (threadIdx.x == 0) w = load_out(a.sc);
   if (j < H->count) {
-    const float s = vec_job_total(a.partials + D[j].tile_start, D[j].ntiles, D[j].per_item);
+    const float s = vec_job_total(a.partials + D[j].tile_start, D[j].ntiles,
+                                  H->planned == kVecPlanned ? D[j].per_item : 1u);
     if ((threadIdx.x & 63) == 0) {
       if (a.arrivals)
         put_partial(&D[j].sum, s);

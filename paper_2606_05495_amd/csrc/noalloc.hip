@@ -122,6 +122,7 @@ __global__ __launch_bounds__(kNaPlanThreads) void k_vec_noalloc_plan(VecPlanArgs
     H->count = a.count;
     H->total_tiles = carry;
     H->claim = vec_claim(s_elems, carry, a.grid);
+    H->planned = kVecPlanned;
     *a.work = 0u;
   }
 }

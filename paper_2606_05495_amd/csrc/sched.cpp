@@ -1038,6 +1038,7 @@ class Context {
       }
       H->total_tiles = ts;
       H->claim = vec_claim(elems, ts, pl.grid);
+      H->planned = kVecPlanned;
       set_job_args a;
       std::memset(&a, 0, sizeof(a));
       a.host_in = tab;
@@ -1127,6 +1128,7 @@ class Context {
       H->count = (uint32_t)take.size();
       H->total_tiles = ts;
       H->claim = vec_claim(elems, ts, t.grid > 0 ? (uint32_t)t.grid : (uint32_t)kVecBatchGrid);
+      H->planned = kVecPlanned;
       set_job_args b;
       std::memset(&b, 0, sizeof(b));
       b.host_in = R.tab;

@@ -60,6 +60,11 @@ SETRT_HD inline uint32_t vec_unit_elems(uint32_t item_elems, int block) {
   const uint32_t least = 64u * (uint32_t)block;
   return item_elems / 4u >= least ? item_elems / 4u : item_elems / 2u >= least ? item_elems / 2u : item_elems;
 }
+// The same for a table submitted by hand, whose items may be of any size: the
+// library's split where it is even, else the whole item.
+SETRT_HD inline uint32_t vec_hand_unit(uint32_t item_elems, int block) {
+  return item_elems % 1024u ? item_elems : vec_unit_elems(item_elems, block);
+}
 // Units a block claims at a time.  A claim is an atomic on one word of the whole
 // device, which takes them at about 70 a microsecond: units of 1024 elements,
 // claimed one by one, cannot run faster than 0.6 TB/s.  So short units are
