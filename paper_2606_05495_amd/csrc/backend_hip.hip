@@ -584,6 +584,9 @@ class HipBackend : public Backend {
       if (lib_call) return library_stage(p, sl, st);
       return hipLaunchKernel(sl.func[ks], sl.grid[ks], dim3(sl.block[ks]), sl.argv[ks], 0, st);
     };
+    // A batch's input is its descriptor table, which a later timing of its stages reads:
+    // empty, not what the last stage or an output copy left in the placeholder.
+    if (copy_in && p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32) std::memset(p.placeholder, 0, in_b);
     // the jobs' own output buffers may be gone by now
     if (writes_out(p.t))
       for (Slot& s : p.slots) set_out(s, p.t.pipeline, p.placeholder);

@@ -296,11 +296,9 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     std::lock_guard<std::mutex> l(e->mu);
     g = ++e->recorded;
   }
-  enqueue(s, [e, g] {
-    {
-      std::lock_guard<std::mutex> l(e->mu);
-      if (e->completed < g) e->completed = g;
-    }
+  enqueue(s, [e, g] {  // told under the lock: who waited may destroy the event
+    std::lock_guard<std::mutex> l(e->mu);
+    if (e->completed < g) e->completed = g;
     e->cv.notify_all();
   });
   return hipSuccess;

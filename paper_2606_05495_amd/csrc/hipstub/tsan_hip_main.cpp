@@ -177,6 +177,51 @@ int run_vectors() {
   return rc;
 }
 
+// Stage timings of a batch template after jobs, in an order that once left the
+// placeholder's output header where the next timing looks for a descriptor table.
+int run_stage_timing() {
+  set_config cfg;
+  std::memset(&cfg, 0, sizeof(cfg));
+  cfg.abi_version = SET_ABI_VERSION;
+  cfg.mode = SET_MODE_SET;
+  cfg.backend = SET_BACKEND_HIP;
+  cfg.num_workers = 1;
+  cfg.slots_per_worker = 2;
+  set_ctx* c = nullptr;
+  if (set_ctx_create(&cfg, &c) != SET_OK) return 1;
+  static float pool[1 << 10];
+  set_job_template t;
+  std::memset(&t, 0, sizeof(t));
+  t.pipeline = SET_PIPE_SAXPY_BATCH_F32;
+  t.max_n = 1 << 10;
+  t.dev_x_pool = pool;
+  t.dev_y_pool = pool;
+  t.pool_len = 1 << 10;
+  t.batch_max = 16;
+  t.tiles_max = 256;
+  uint64_t slot_bytes = 0, total = 0;
+  set_template_footprint(&cfg, &t, &slot_bytes, &total);
+  void* arena = nullptr;
+  if (hipMalloc(&arena, total) != hipSuccess) return 1;
+  t.arena = arena;
+  t.arena_bytes = total;
+  int tid = -1, rc = 0;
+  if (set_template_define(c, &t, &tid) != SET_OK) return 2;
+  std::vector<set_vec_job> jobs(16, set_vec_job{0, 0, 100, 1.0f, 0});
+  std::vector<float> res(jobs.size());
+  for (int rep = 0; rep < 3; ++rep)
+    if (set_run_vector_jobs(c, tid, jobs.data(), jobs.size(), res.data(), nullptr, nullptr) != SET_OK) rc = 3;
+  double us = 0.0;
+  for (int stage : {1, SET_STAGE_OUTPUT_COPY, SET_STAGE_INPUT_COPY})
+    if (set_time_stage(c, tid, stage, -1, 4, &us) != SET_OK) rc = 4;
+  for (uint64_t i = 0; i + 4 <= total; i += 4)
+    if (*reinterpret_cast<const uint32_t*>(static_cast<const char*>(arena) + i) == SET_OUT_MAGIC) rc = 5;
+  if (rc) std::printf("stage timing: %s\n", rc == 5 ? "an output header in a slot's table" : set_last_error(c));
+  set_ctx_destroy(c);
+  (void)hipFree(arena);
+  return rc;
+}
+
 }  // namespace
 
 int main() {
@@ -221,6 +266,7 @@ int main() {
     ++i;
   }
   if (run_vectors() != 0) rc |= 1 << i;
+  if (run_stage_timing() != 0) rc |= 1 << 28;
   const uint64_t hz = hipstub::updates_while_in_flight();
   std::printf("stub: %llu launches, %llu executable updates overlapping a launch of the same executable\n",
               (unsigned long long)hipstub::launches(), (unsigned long long)hz);
