@@ -138,6 +138,11 @@ __global__ __launch_bounds__(kBlock) void k_vec_noalloc_totals(NaTotalsArgs a) {
   if ((threadIdx.x & 63) == 0) a.results[j] = D[j].n == 0 ? __builtin_nanf("") : s;
 }
 
+bool overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes) {
+  const uint64_t x = reinterpret_cast<uint64_t>(a), y = reinterpret_cast<uint64_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
+
 std::mutex g_na_mu;
 std::atomic<unsigned char*> g_na_ptr[kNaMaxDevices];
 
@@ -217,7 +222,11 @@ int run_noalloc(int device, hipStream_t stream, const float* x, const float* y, 
     pa.split = count * worst_units <= kNaMaxItems;
     const uint64_t most_tiles = count * (pa.split ? worst_units : worst);
     pa.grid = grid ? grid : (uint32_t)std::min<uint64_t>(kNaGrid, most_tiles);
-    const bool is_short = worst <= kVecShortItems && longest_item <= kVecShortItem && grid == 0;
+    // The one kernel of short jobs writes results while other blocks still read: where
+    // they replace what it reads, the call takes the kernels that read everything first.
+    const bool reused = overlap(results, 4 * count, jobs, sizeof(set_vec_job) * count) ||
+                        overlap(results, 4 * count, x, 4 * pool_len) || overlap(results, 4 * count, y, 4 * pool_len);
+    const bool is_short = worst <= kVecShortItems && longest_item <= kVecShortItem && grid == 0 && !reused;
     if (is_short) {
       VecShortArgs sa{pa, x, y, results};
       hipLaunchKernelGGL(k_vec_short_jobs, dim3((unsigned)count), dim3(64 * (unsigned)worst), 0, stream, sa);
