@@ -33,6 +33,23 @@ from typing import Iterable, List, Sequence, Tuple
 
 Interval = Tuple[float, float]
 
+# Stages that combine a job's partial results and write them to host memory.
+OUTPUT_STAGES = ("k_copy_out_hist256", "k_copy_out_sobel", "k_copy_out_vec")
+
+
+def is_copy_name(name: str) -> bool:
+    """A copy between host and device, by kernel or DMA, in either direction."""
+    return "copy" in name.lower() and not any(s in name for s in OUTPUT_STAGES)
+
+
+def is_input_name(name: str) -> bool:
+    """A copy known to be host-to-device: the first thing of a job."""
+    return "k_copy_in" in name or name == "dma_copy_h2d"
+
+
+def is_tail_name(name: str) -> bool:
+    return "done_flag" in name
+
 
 def union_length(intervals: Iterable[Interval]) -> float:
     iv = sorted((a, b) for a, b in intervals if b > a)
@@ -118,16 +135,17 @@ def timeline_metrics(kernels: Sequence[Interval], copies_h2d: Sequence[Interval]
 
 
 def stream_gaps(kernels: Sequence[Interval], streams: Sequence, names: Sequence[str] = (),
-                is_copy=lambda n: "copy" in n.lower(), is_tail=lambda n: "done_flag" in n) -> dict:
+                is_copy=is_copy_name, is_tail=is_tail_name, is_input=is_input_name) -> dict:
     """Gaps between consecutive kernels of the same stream.
 
     On one stream a job's kernels run in order (host-to-device copy, stages,
-    device-to-host copy, optionally a completion-word kernel), so a gap there
+    device-to-host copy where the last stage does not write the output itself,
+    optionally a completion-word kernel), so a gap there
     is dispatch latency: either between two kernels of one job (dependency
     resolution inside a graph) or between one job's last kernel and the next
-    job's first copy (the launch path).  A copy that follows a copy or a
-    completion-word kernel starts a new job; every other pair is a gap inside
-    a job."""
+    job's first copy (the launch path).  A host-to-device copy starts a new job,
+    and so does a copy that follows a copy or a completion-word kernel; every
+    other pair is a gap inside a job."""
     by = {}
     for i, (iv, s) in enumerate(zip(kernels, streams)):
         by.setdefault(s, []).append((iv[0], iv[1], names[i] if names else ""))
@@ -137,7 +155,7 @@ def stream_gaps(kernels: Sequence[Interval], streams: Sequence, names: Sequence[
         for (a0, a1, an), (b0, b1, bn) in zip(ks, ks[1:]):
             g = max(0.0, b0 - a1)
             allg.append(g)
-            if names and is_copy(bn) and (is_copy(an) or is_tail(an)):
+            if names and (is_input(bn) or is_copy(bn) and (is_copy(an) or is_tail(an))):
                 inter.append(g)
             else:
                 intra.append(g)
@@ -146,16 +164,13 @@ def stream_gaps(kernels: Sequence[Interval], streams: Sequence, names: Sequence[
             "mean_job_boundary_gap": mean(inter) if names else None}
 
 
-def eq_terms(kernels: Sequence[Interval], streams: Sequence, names: Sequence[str],
-             is_copy=lambda n: "copy" in n.lower(), is_tail=lambda n: "done_flag" in n) -> dict:
-    """Per-job terms of the overhead model (Section 3.1, Eq. 1-2) from one
-    stream's kernel sequence [input copy, stages..., output copy (, completion
-    word)]: t_in, t_k (sum of stage durations), t_out, and the gaps t_in-k
-    (input copy end to first stage), Delta t_k (between stages) and t_k-out
-    (last stage to output copy).  Segments without that shape, or whose stage
-    count differs from the most common one (chains interleaved on one
-    stream), are skipped; `jobs` counts the ones used.  Means in the input's
-    time unit."""
+def job_chains(kernels: Sequence[Interval], streams: Sequence, names: Sequence[str],
+               is_copy=is_copy_name, is_tail=is_tail_name, is_input=is_input_name) -> list:
+    """The jobs of every stream's kernel sequence, each as (chain, has_output_copy)
+    with the chain a list of (start, end, name): [input copy, stages..., output
+    copy], or [input copy, stages...] where the last stage writes the output to
+    host memory itself (then the input copy has to be known as one).  Completion
+    words are left out, and so are segments of any other shape."""
     by = {}
     for iv, s, n in zip(kernels, streams, names):
         by.setdefault(s, []).append((iv[0], iv[1], n))
@@ -164,31 +179,49 @@ def eq_terms(kernels: Sequence[Interval], streams: Sequence, names: Sequence[str
         ks.sort()
         seg = []
         for a, b, n in ks + [(None, None, "")]:
-            starts_job = n == "" or (is_copy(n) and (not seg or is_copy(seg[-1][2]) or is_tail(seg[-1][2])))
+            starts_job = n == "" or is_input(n) or \
+                (is_copy(n) and (not seg or is_copy(seg[-1][2]) or is_tail(seg[-1][2])))
             if starts_job and seg:
                 body = [x for x in seg if not is_tail(x[2])]
-                if len(body) >= 3 and is_copy(body[0][2]) and is_copy(body[-1][2]) and \
-                        not any(is_copy(x[2]) for x in body[1:-1]):
-                    cands.append(body)
+                if len(body) >= 2 and is_copy(body[0][2]) and not any(is_copy(x[2]) for x in body[1:-1]):
+                    out = is_copy(body[-1][2])
+                    if len(body) >= 3 if out else is_input(body[0][2]):
+                        cands.append((body, out))
                 seg = []
             if n:
                 seg.append((a, b, n))
+    return cands
+
+
+def eq_terms(kernels: Sequence[Interval], streams: Sequence, names: Sequence[str],
+             is_copy=is_copy_name, is_tail=is_tail_name, is_input=is_input_name) -> dict:
+    """Per-job terms of the overhead model (Section 3.1, Eq. 1-2) from one
+    stream's kernel sequence [input copy, stages..., output copy (, completion
+    word)]: t_in, t_k (sum of stage durations), t_out, and the gaps t_in-k
+    (input copy end to first stage), Delta t_k (between stages) and t_k-out
+    (last stage to output copy).  Where the last stage writes the output itself,
+    its time is in t_k, and t_out and t_k-out are 0.  Segments without that shape, or whose stage
+    count differs from the most common one (chains interleaved on one
+    stream), are skipped; `jobs` counts the ones used.  Means in the input's
+    time unit."""
+    cands = job_chains(kernels, streams, names, is_copy, is_tail, is_input)
     acc = {"t_in": 0.0, "t_k": 0.0, "t_out": 0.0, "t_in_k": 0.0, "delta_t_k": 0.0, "t_k_out": 0.0}
     jobs = 0
     if cands:
         counts = {}
-        for body in cands:
-            counts[len(body)] = counts.get(len(body), 0) + 1
-        m = max(counts, key=lambda k: (counts[k], -k))
-        for body in cands:
-            if len(body) != m:
+        for body, out in cands:
+            counts[len(body), out] = counts.get((len(body), out), 0) + 1
+        m = max(counts, key=lambda k: (counts[k], -k[0]))
+        for body, out in cands:
+            if (len(body), out) != m:
                 continue
-            st = body[1:-1]
+            st = body[1:-1] if out else body[1:]
             acc["t_in"] += body[0][1] - body[0][0]
-            acc["t_out"] += body[-1][1] - body[-1][0]
+            if out:
+                acc["t_out"] += body[-1][1] - body[-1][0]
+                acc["t_k_out"] += max(0.0, body[-1][0] - st[-1][1])
             acc["t_k"] += sum(b1 - a1 for a1, b1, _ in st)
             acc["t_in_k"] += max(0.0, st[0][0] - body[0][1])
-            acc["t_k_out"] += max(0.0, body[-1][0] - st[-1][1])
             acc["delta_t_k"] += sum(max(0.0, st[i + 1][0] - st[i][1]) for i in range(len(st) - 1))
             jobs += 1
     out = {k: (v / jobs if jobs else None) for k, v in acc.items()}
@@ -204,6 +237,13 @@ def inter_batch_gaps(h2d: Sequence[Interval], d2h: Sequence[Interval], batch: in
     starts = [hs[i * batch][0] for i in range(nb)]
     ends = [ds[(i + 1) * batch - 1][1] for i in range(nb)]
     return [starts[i + 1] - ends[i] for i in range(nb - 1)]
+
+
+def inter_batch_gaps_of_stages(h2d: Sequence[Interval], kernels: Sequence[Interval], batch: int) -> List[float]:
+    """Eq. 3 where the jobs' last stages write the outputs: a batch ends with the
+    last kernel that started before the next batch's first copy."""
+    starts = [a for a, _ in sorted(h2d)][::batch]
+    return [s - max(b for a, b in kernels if a < s) for s in starts[1:]]
 
 
 # ------------------------------------------------------------------ rocprofv3 CSV
@@ -293,7 +333,14 @@ def analyze_dir(dirpath: str, batch: int = 0, library_window: bool = False) -> d
     # input and output copies of either kind: DMA copies and the copy kernels
     # (k_copy_in host-to-device, k_copy_out device-to-host)
     cin = h2d + [iv for iv, n in zip(kernels, names) if "k_copy_in" in n]
-    cout = d2h + [iv for iv, n in zip(kernels, names) if "k_copy_out" in n]
+    copied = d2h + [iv for iv, n in zip(kernels, names) if "k_copy_out" in n]
+    # jobs whose last stage writes the output: that stage, for templates (told by
+    # their first stage) most of whose jobs end so
+    ends = {}
+    for body, out in job_chains(ev, ev_streams, ev_names):
+        ends.setdefault(body[1][2], []).append(None if out else body[-1])
+    cout = copied + [(x[0], x[1]) for v in ends.values() if 2 * v.count(None) < len(v) for x in v
+                     if x is not None and "k_copy_out" not in x[2]]
     span = m.get("span") or 0.0
     if cin and span > 0:
         m["h2d_idle_fraction"] = 1.0 - union_length(cin) / (span * 1e3)
@@ -301,7 +348,7 @@ def analyze_dir(dirpath: str, batch: int = 0, library_window: bool = False) -> d
         # both directions on the link at once, as a share of the time either is
         m["h2d_d2h_overlap_fraction"] = overlap_length(cin, cout) / union_length(cin + cout)
     if batch and cin and cout:
-        g = inter_batch_gaps(cin, cout, batch)
+        g = inter_batch_gaps(cin, copied, batch) if copied else inter_batch_gaps_of_stages(cin, ev, batch)
         m["mean_inter_batch_us"] = (sum(g) / len(g) / 1e3) if g else None
     return m
 
