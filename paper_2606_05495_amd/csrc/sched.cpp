@@ -130,6 +130,7 @@ class Context {
   std::mutex stage_mu;
   std::condition_variable stage_cv;       // submitter waits for jobs
   std::condition_variable stage_room_cv;  // producers wait for room
+  int stage_waiters = 0;                  // producers that do
   std::deque<JobRec*> staging;
   int staging_cap = 4096;
 
@@ -552,6 +553,8 @@ class Context {
   // job blocked by the budget is never overtaken, so large jobs cannot starve.
   // Returns 1 if a job was admitted, 0 if none could be, -1 on a bind error.
   static constexpr size_t kAdmitWindow = 32;
+  static constexpr uint64_t kRoomWakeNs = 200000;
+  uint64_t t_room_wake = 0;  // the submitter's own
 
   int admit_one() {
     JobRec* window[kAdmitWindow];
@@ -573,18 +576,28 @@ class Context {
         continue;
       }
       size_t left;
+      bool awaited;
       {
         std::lock_guard<std::mutex> g(stage_mu);
         staging.erase(std::find(staging.begin(), staging.begin() + (k + 1), j));
         left = staging.size();
+        awaited = stage_waiters > 0;
       }
-      // Callers that wait for room are woken when half of it is free, not for every
-      // entry: a stream longer than the ring was handed over a job to a wake-up, and
-      // its short jobs took 9-10.7 us each (8.5-9.8 as graphs) where a stream that
-      // fits takes 2.9; now 2.7-3.0.  A ring within a few windows of admission keeps
-      // the wake-up for every entry, so that other templates' jobs come into view.
-      if (left <= (size_t)(staging_cap >= 4 * (int)kAdmitWindow ? staging_cap / 2 : staging_cap - 1))
-        stage_room_cv.notify_all();
+      // Callers that wait for room are woken when half of it is free and at most every
+      // kRoomWakeNs before that, not for every entry: a stream longer than the ring was
+      // handed over a job to a wake-up, and its short jobs took 9-10.7 us each (8.5-9.8
+      // as graphs) where a stream that fits takes 2.9; now 2.7-3.0.  Jobs that take
+      // longer than kRoomWakeNs wake them one by one, as soon as each makes room.  A
+      // ring within a few windows of admission keeps the wake-up for every entry, so
+      // that other templates' jobs come into view.
+      if (awaited) {
+        const uint64_t now = now_ns();
+        if (left <= (size_t)(staging_cap >= 4 * (int)kAdmitWindow ? staging_cap / 2 : staging_cap - 1) ||
+            now - t_room_wake >= kRoomWakeNs) {
+          t_room_wake = now;
+          stage_room_cv.notify_all();
+        }
+      }
       if (bind_to(j, w, s) != SET_OK) {
         release_slot(j->tmpl, w, s);
         if (cfg.mem_budget_bytes) mem_in_use -= j->footprint;
@@ -855,10 +868,12 @@ class Context {
           free_job(j);
           return SET_EAGAIN;
         }
-        // also looked at every millisecond: other callers may keep the ring between
-        // half full, where those that wait are woken, and full
+        // also looked at every millisecond: an entry that made room within kRoomWakeNs
+        // of the last wake-up may be the last for a while
         const auto room = [&] { return (int)staging.size() < staging_cap || stopping.load(); };
+        ++stage_waiters;
         while (!room()) timed_wait(stage_room_cv, lk, std::chrono::milliseconds(1), room);
+        --stage_waiters;
         if (stopping.load()) {
           lk.unlock();
           free_job(j);
