@@ -1192,6 +1192,8 @@ class HipBackend : public Backend {
     if (e == hipSuccess && poisons(p)) e = launch_stress(p, sl, true, st);
     if (e == hipSuccess && p.words && !flag_in_stage(p))
       e = run((const void*)&k_done_flag, dim3(1), 64, sl.flag_argv);
+    // the job fails: what was launched of it still uses the caller's buffers
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);
     return e;
   }
 

@@ -152,4 +152,6 @@ void register_kernel(void (*f)(A)) {
 // Counters the stress driver reads.
 uint64_t launches();
 uint64_t updates_while_in_flight();
+// Make the nth kernel launch from here on (1: the next) fail.
+void fail_launch(int nth);
 }  // namespace hipstub

@@ -27,10 +27,12 @@ std::unordered_map<const void*, Kernel>& registry() {
   return r;
 }
 std::atomic<uint64_t> g_launches{0}, g_hazards{0}, g_walk{0};
+std::atomic<int> g_fail_in{0};
 }  // namespace
 void register_kernel(const void* func, size_t arg_bytes, Invoke run) { registry()[func] = Kernel{arg_bytes, run}; }
 uint64_t launches() { return g_launches.load(); }
 uint64_t updates_while_in_flight() { return g_hazards.load(); }
+void fail_launch(int nth) { g_fail_in.store(nth); }
 const Kernel* find_kernel(const void* f) {
   auto it = registry().find(f);
   return it == registry().end() ? nullptr : &it->second;
@@ -258,6 +260,7 @@ hipError_t hipLaunchKernel(const void* func, dim3 grid, dim3 block, void** args,
   const hipstub::Kernel* k = hipstub::find_kernel(func);
   if (!k || !args || !args[0]) return hipErrorInvalidValue;
   if (foreign_capture(s)) return hipErrorUnknown;
+  if (hipstub::g_fail_in.load() > 0 && hipstub::g_fail_in.fetch_sub(1) == 1) return hipErrorUnknown;
   std::vector<char> bytes((const char*)args[0], (const char*)args[0] + k->bytes);  // copied at launch
   if (s->cap) {
     hipGraphNode* n = s->cap->add(s->cap_last ? &s->cap_last : nullptr, s->cap_last ? 1 : 0);

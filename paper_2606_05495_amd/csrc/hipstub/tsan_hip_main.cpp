@@ -8,6 +8,7 @@
 // ThreadSanitizer reports races itself, and the stub counts graph-executable
 // updates that overlapped a queued or running launch of the same executable.
 #include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <thread>
@@ -222,6 +223,48 @@ int run_stage_timing() {
   return rc;
 }
 
+// A chain whose last launch fails is not reported as failed before what was launched
+// of it has ended: its output buffer is the caller's again from then on.
+int run_failed_launch(int mode) {
+  set_config cfg;
+  std::memset(&cfg, 0, sizeof(cfg));
+  cfg.abi_version = SET_ABI_VERSION;
+  cfg.mode = mode;
+  cfg.backend = SET_BACKEND_HIP;
+  cfg.num_workers = 1;
+  cfg.slots_per_worker = 1;
+  cfg.callback_mode = SET_CB_HOST_FLAG;
+  set_ctx* c = nullptr;
+  if (set_ctx_create(&cfg, &c) != SET_OK) return 1;
+  set_job_template t;
+  std::memset(&t, 0, sizeof(t));
+  t.pipeline = SET_PIPE_HOTSPOT_F32;
+  t.width = t.height = 16;
+  t.max_n = 1;
+  t.stress_delay_us = 20000;
+  t.flags = SET_TF_POISON;
+  int tid = -1;
+  if (set_template_define(c, &t, &tid) != SET_OK) return 2;
+  alignas(64) static char in[8 * 256], out[64 + 4 * 256];
+  set_job_args a;
+  std::memset(&a, 0, sizeof(a));
+  a.host_in = in;
+  a.in_bytes = sizeof(in);
+  a.host_out = out;
+  a.out_bytes = sizeof(out);
+  a.worker_hint = -1;
+  hipstub::fail_launch(4);  // input copy, delay, step; the poison fill
+  (void)set_submit(c, tid, &a, 0, nullptr);
+  int rc = set_drain(c, -1) != SET_OK ? 0 : 3;
+  std::memset(out, 0x5A, sizeof(out));
+  std::this_thread::sleep_for(std::chrono::milliseconds(100));
+  for (char v : out)
+    if (v != 0x5A) rc = 4;
+  if (rc) std::printf("failed launch, mode %d: %s\n", mode, rc == 3 ? "not reported" : "its output was written afterwards");
+  set_ctx_destroy(c);
+  return rc;
+}
+
 }  // namespace
 
 int main() {
@@ -267,6 +310,8 @@ int main() {
   }
   if (run_vectors() != 0) rc |= 1 << i;
   if (run_stage_timing() != 0) rc |= 1 << 28;
+  if (run_failed_launch(SET_MODE_SET) != 0) rc |= 1 << 27;
+  if (run_failed_launch(SET_MODE_SYNC) != 0) rc |= 1 << 26;
   const uint64_t hz = hipstub::updates_while_in_flight();
   std::printf("stub: %llu launches, %llu executable updates overlapping a launch of the same executable\n",
               (unsigned long long)hipstub::launches(), (unsigned long long)hz);
