@@ -813,7 +813,8 @@ class HipBackend : public Backend {
       case SET_PIPE_BOX_HIST_U8: {
         if (!(t.flags & SET_TF_DEBUG)) {
           const unsigned bb = box_hist_blocks(h, w);
-          sl.boxh = BoxHistArgs{(const uint8_t*)(b + L.in), h, w, (uint32_t*)(b + L.scratch), sc.hdr, JobScalars{}};
+          sl.boxh = BoxHistArgs{(const uint8_t*)(b + L.in), h, w, box_hist_shift(h, w), (uint32_t*)(b + L.scratch), sc.hdr,
+                                JobScalars{}};
           sl.histf = HistFinalArgs{(const uint32_t*)(b + L.scratch), bb, (uint32_t*)payload, sc};
           stage((const void*)&k_box_hist_u8, dim3(bb), &sl.boxh, (unsigned)kBoxHistBlock);
           stage(wo ? (const void*)&k_copy_out_hist256 : (const void*)&k_hist256_final, dim3(1), &sl.histf,

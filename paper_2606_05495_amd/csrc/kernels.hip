@@ -317,8 +317,8 @@ __global__ __launch_bounds__(kBlock) void k_job_end(JobEndArgs a) {
 
 // ------------------------------------------------------------------ box sum, floor(s / 9) and histogram in one
 // For templates that return the histogram alone: the sums and quotients stay in
-// registers.  A thread takes 4 pixels of a row, 16 threads a row of the block's
-// 64 x 64 tile.  Of each of its three input rows it loads the 8 bytes from one
+// registers.  A thread takes 4 pixels of a row of the block's tile, which is 64 x 64
+// or, for narrow images, wider or taller (box_hist_shift).  Of each of its three input rows it loads the 8 bytes from one
 // left of its pixels, at any alignment (before the first and past the last row
 // of the image they reach into the slot around it, and are masked), and adds
 // them column-wise two to a word.  Quotients go to LDS bins, four copies.  The
@@ -336,10 +336,11 @@ __global__ __launch_bounds__(kBoxHistBlock) void k_box_hist_u8(BoxHistArgs a) {
   (&wh[0][0])[tid] = 0u;
   __syncthreads();
   uint32_t* bins = wh[(tid >> 6) & 3];
-  const int tiles_x = (a.w + kBoxHistTile - 1) / kBoxHistTile, tiles_y = (a.h + kBoxHistTile - 1) / kBoxHistTile;
+  const int lw = a.shift + 2, lh = __builtin_ctz(kBoxHistBlock) - a.shift;  // log2 of the tile's sides
+  const int tiles_x = (a.w + (1 << lw) - 1) >> lw, tiles_y = (a.h + (1 << lh) - 1) >> lh;
   for (int t = blockIdx.x; t < tiles_x * tiles_y; t += gridDim.x) {
     const int by = t / tiles_x, bx = t - by * tiles_x;
-    const int x = bx * kBoxHistTile + 4 * (tid & 15), y = by * kBoxHistTile + (tid >> 4);
+    const int x = (bx << lw) + 4 * (tid & ((1 << a.shift) - 1)), y = (by << lh) + (tid >> a.shift);
     if (x >= a.w || y >= a.h) continue;
     uint32_t even0 = 0, odd0 = 0, even1 = 0, odd1 = 0;  // columns x-1, x+1 | x, x+2 | x+3 | x+4
 #pragma unroll

@@ -32,6 +32,7 @@ struct BoxArgs {
 struct BoxHistArgs {
   const uint8_t* in;
   int h, w;
+  int shift;           // box_hist_shift(h, w)
   uint32_t* partials;  // [grid][256]
   DevSlotHdr* hdr;
   JobScalars js;

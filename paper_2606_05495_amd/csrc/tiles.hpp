@@ -109,15 +109,26 @@ inline unsigned hist_blocks(int64_t npix) {
   return (unsigned)((npix + (int64_t)kBlock * kHistPerThread - 1) / ((int64_t)kBlock * kHistPerThread));
 }
 // Box sums, quotients and histogram in one kernel (templates without
-// intermediate images): 64 x 64 tiles, at most a block for each compute unit
+// intermediate images): tiles of 4096 pixels, at most a block for each compute unit
 // (one block combines the partial rows: of 2048^2 pixels 1024 rows took it 34
 // us, 256 take it 4.6) and for each partial row of the slot's scratch, which
-// hist_blocks sizes (ragged grids have more tiles).
-constexpr int kBoxHistTile = 64;
+// hist_blocks sizes (ragged grids have more tiles).  A tile is 64 x 64, four
+// pixels to a thread, unless half of it would lie beside a narrow image: it is then
+// halved in width and doubled in height, or the other way round.  One job, us, at
+// 64 x 64 / so: 1 x 262144 72 / 28, 262144 x 1 59 / 26, 65536 x 4 33 / 26 (the three
+// kernels that return the images 44, 34, 32).
 constexpr int kBoxHistBlock = 1024;
 constexpr int kHistFinalBlock = 1024;
+// log2 of the threads across a tile: 4 << s columns, kBoxHistBlock >> s rows.
+inline int box_hist_shift(int h, int w) {
+  int s = 4;
+  while (s > 0 && w <= 2 << s) --s;
+  while (s < 10 && 2 * (int64_t)h <= kBoxHistBlock >> s) ++s;
+  return s;
+}
 inline unsigned box_hist_blocks(int h, int w) {
-  const uint64_t t = (uint64_t)((w + kBoxHistTile - 1) / kBoxHistTile) * ((h + kBoxHistTile - 1) / kBoxHistTile);
+  const int s = box_hist_shift(h, w), tw = 4 << s, th = kBoxHistBlock >> s;
+  const uint64_t t = (((uint64_t)w + tw - 1) / tw) * (((uint64_t)h + th - 1) / th);
   const unsigned hb = hist_blocks((int64_t)h * w);
   const uint64_t b = t < hb ? t : hb;
   return (unsigned)(b < 256 ? b : 256);
