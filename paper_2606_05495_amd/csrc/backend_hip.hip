@@ -938,7 +938,7 @@ class HipBackend : public Backend {
         sl.scan_r = ScanReduceArgs{(const int32_t*)(b + L.in), (int64_t*)sb, T, sc.hdr, JobScalars{}};
         sl.scan_r.js.n = t.max_n;
         sl.scan_s = ScanSpineArgs{(const int64_t*)sb, (int64_t*)(sb + q8), sc, t.max_n};
-        const int prefix = scan_prefix(t.max_n);
+        const int prefix = scan_prefix(t);
         sl.scan_d = ScanDownArgs{(const int32_t*)(b + L.in), (const int64_t*)(prefix == SCAN_FROM_SPINE ? sb + q8 : sb),
                                  (void*)payload, (t.flags & SET_TF_SCAN_LOW32) ? 1 : 0, sc, JobScalars{}};
         sl.scan_d.js.n = t.max_n;

@@ -342,7 +342,7 @@ int pipeline_sizes(const set_job_template& t, TemplateSizes* out) {
     case SET_PIPE_SCAN_I32_I64: {
       const uint64_t T = scan_tiles(t.max_n);
       const uint64_t ob = ((t.flags & SET_TF_SCAN_LOW32) ? 4 : 8) * t.max_n;
-      const int prefix = scan_prefix(t.max_n);
+      const int prefix = scan_prefix(t);
       if (prefix != SCAN_FROM_INPUT) stage("scan_reduce_i32", 4 * t.max_n + 8 * T);
       if (prefix == SCAN_FROM_SPINE) stage("scan_spine_i64", 16 * T + 64);
       stage("scan_down_i32_i64", 4 * t.max_n + 8 * T + ob);

@@ -264,12 +264,15 @@ SETRT_HD inline unsigned scan_tiles(uint64_t n) { return (unsigned)((n + kScanTi
 // 16000 341 / 330 / 282, 65000 - / 546 / 488, 100000 842 / 813 / 717, 130000 - / 958 /
 // 860; from there the input is read too often (200000 by one kernel: one job 98 /
 // 104), and output written by the downsweep is held up in its many blocks (2^21,
-// one job 540 / 595, where two kernels and a copy take what three took).
-constexpr unsigned kScanRawTiles = 64, kScanSumTiles = 1024;
+// one job 540 / 595, where two kernels and a copy take what three took).  Where the
+// output goes by a memcpy node or a copy kernel all the same (to_host false), one
+// kernel saves less and its reading shows earlier: 24 jobs, us, three / one, 16384
+// elements 881 / 810, 32768 940 / 916, 50000 1017 / 1040, 131072 1432 / 1600.
+constexpr unsigned kScanRawTiles = 64, kScanRawTilesCopied = 16, kScanSumTiles = 1024;
 enum { SCAN_FROM_INPUT, SCAN_FROM_SUMS, SCAN_FROM_SPINE };
-inline int scan_prefix(uint64_t max_n) {
+inline int scan_prefix(uint64_t max_n, bool to_host) {
   const unsigned t = scan_tiles(max_n);
-  return t <= kScanRawTiles ? SCAN_FROM_INPUT : t <= kScanSumTiles ? SCAN_FROM_SUMS : SCAN_FROM_SPINE;
+  return t <= (to_host ? kScanRawTiles : kScanRawTilesCopied) ? SCAN_FROM_INPUT : t <= kScanSumTiles ? SCAN_FROM_SUMS : SCAN_FROM_SPINE;
 }
 
 // Byte layout of one buffer slot of a template (offsets from the slot base,
