@@ -765,10 +765,9 @@ class HipBackend : public Backend {
     }
   }
 
-  // Arrival words of a one-kernel image template lie where the blurred image
-  // would, which it does not keep: four bytes a pixel, and the words take at most
-  // two a tile, or 256 in all.  A vector batch's lie where its output would, 16
-  // bytes a block of its last kernel.
+  // Arrival words of a one-kernel image template take the blurred image's place in
+  // the layout.  A vector batch's lie where its output would, 16 bytes a block of its
+  // last kernel.
   static bool arrives(const Pipe& p) {
     return one_kernel_image(p.t) || (p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32 && writes_out(p.t));
   }
@@ -778,8 +777,7 @@ class HipBackend : public Backend {
   static uint64_t arrival_room(const Pipe& p) {
     if (p.t.pipeline == SET_PIPE_SAXPY_BATCH_F32)
       return arrival_bytes((p.t.batch_max + kVecFinalJobs - 1) / kVecFinalJobs);
-    const Grid3 g = gauss_sobel_grid((int)p.t.height, (int)p.t.width);
-    return arrival_bytes((uint64_t)g.x * g.y);
+    return arrival_bytes(image_partials(p.t));
   }
   void setup_slot(Pipe& p, Slot& sl, const float taps[3]) {
     const SlotLayout& L = p.L;
@@ -836,7 +834,7 @@ class HipBackend : public Backend {
         sl.gauss = GaussArgs{(const float*)(b + L.in), (float*)(b + L.b1), h, w, taps[0], taps[1], taps[2], sc.hdr,
                              JobScalars{}};
         const Grid3 sg = sobel_grid(h, w);
-        const unsigned nb = (unsigned)sobel_partials(h, w);
+        const unsigned nb = (unsigned)image_partials(t);
         const uint64_t q = ((uint64_t)nb * 4 + 255) / 256 * 256;
         sl.sobel = SobelArgs{(const float*)(b + L.b1), (uint8_t*)(b + L.b2), h, w,
                              t.threshold != 0.f ? t.threshold : 1.0f, (uint32_t*)(b + L.scratch),

@@ -150,6 +150,13 @@ inline bool one_kernel_image(const set_job_template& t) {
   return t.pipeline == SET_PIPE_GAUSS_SOBEL_F32 && !(t.flags & SET_TF_DEBUG) &&
          gauss_sobel_in_one((int)t.height, (int)t.width);
 }
+// Partial counts and sums of an image job: one to a tile of the one kernel, or of the
+// Sobel kernel's blocks or waves.
+inline uint64_t image_partials(const set_job_template& t) {
+  if (!one_kernel_image(t)) return sobel_partials((int)t.height, (int)t.width);
+  const Grid3 g = gauss_sobel_grid((int)t.height, (int)t.width);
+  return (uint64_t)g.x * g.y;
+}
 // Where a scan template's blocks have the sums before their tiles from.
 inline int scan_prefix(const set_job_template& t) {
   return scan_prefix(t.max_n, t.copy_mode != SET_COPY_NODES && !(t.flags & SET_TF_DEBUG));

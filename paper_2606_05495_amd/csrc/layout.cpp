@@ -95,12 +95,6 @@ static SlotLayout layout_of(const set_job_template& t) {
       }
       L.out_cap = o;
       off = up(off + o);
-      if (!dbg) {
-        L.b1 = off;
-        off = up(off + 2 * npix);
-        L.b2 = off;
-        off = up(off + npix);
-      }
       L.scratch = off;
       L.scratch_bytes = up((uint64_t)hist_blocks((int64_t)npix) * 256 * 4);  // per-block partial histograms
       off = up(off + L.scratch_bytes);
@@ -122,13 +116,16 @@ static SlotLayout layout_of(const set_job_template& t) {
       }
       L.out_cap = o;
       off = up(off + o);
-      if (!dbg) {
+      if (one_kernel_image(t)) {
+        L.b1 = L.b2 = off;  // arrival words
+        off = up(off + arrival_bytes(image_partials(t)));
+      } else if (!dbg) {
         L.b1 = off;
         off = up(off + 4 * npix);
         L.b2 = off;
         off = up(off + npix);
       }
-      const uint64_t nb = sobel_partials((int)t.height, (int)t.width);
+      const uint64_t nb = image_partials(t);
       L.scratch = off;
       L.scratch_bytes = up(nb * 4) + up(nb * 4);  // partial counts, partial sums
       off = up(off + L.scratch_bytes);

@@ -284,7 +284,7 @@ struct SlotLayout {
   uint64_t in_cap;
   uint64_t out;        // output block: set_out_header + payload (+ debug images)
   uint64_t out_cap;
-  uint64_t b1, b2;     // intermediates (box: S, Q; gauss: blur, mask)
+  uint64_t b1, b2;     // intermediates (box: S, Q in debug templates; gauss: blur, mask, or arrival words)
   uint64_t scratch;    // partials, counters, tile states
   uint64_t scratch_bytes;
   uint64_t tail;       // tail canary
