@@ -192,7 +192,8 @@ enum set_pipeline {
 enum set_copy_mode {
     SET_COPY_KERNELS = 0, /* small-grid copy kernels, nodes of the job's graph, that pull the input from /
                              push the output to pinned host memory; host buffers must be 16-byte aligned.
-                             Small outputs (a histogram, sums, a batch's results, a scan of max_n or a
+                             Small outputs (a histogram, sums, the results of a batch template with
+                             batch_max of up to 1024, a scan of max_n or a
                              thermal grid of up to 131072; without SET_TF_DEBUG) have no
                              copy: the last stage writes them to the host buffer, also in SET_COPY_ASYNC_IN.
                              Default: ROCm runs graph memcpy nodes as large-grid blit kernels that crowd
@@ -417,8 +418,9 @@ int set_template_footprint(const set_config *cfg, const set_job_template *t,
  * arena and build + instantiate + upload one graph per slot whose nodes hold
  * placeholders for per-job arguments (Section 4.1).  In batch-sync mode the
  * batch graph is built instead.  In SET mode no graph is built for a template
- * whose jobs are at most six launches, copy less than 1 MiB in all and have
- * their output written by a kernel, unless it asks for a captured graph
+ * whose jobs are at most six launches (stages and copies; a completion word's
+ * kernel and those of the stress options come on top), copy less than 1 MiB in
+ * all and have their output written by a kernel, unless it asks for a captured graph
  * (SET_TF_CAPTURE, library calls) or is a vector batch with SET_COPY_ASYNC_IN:
  * its kernels are launched directly.  *template_id receives the id (0, 1, ...).
  * Must be called before any submit of that template. */
@@ -537,7 +539,8 @@ int set_run_vector_jobs(set_ctx *c, int template_id, const set_vec_job *jobs, ui
  *   stream's work before the next synchronisation point has finished.
  * dev_x_pool, dev_y_pool: device float pools of pool_len elements each.
  * dev_jobs: device array of count set_vec_job; dev_results: device float
- *   array of count results, in job order.  Both caller-owned.
+ *   array of count results, in job order.  Both caller-owned.  The results may
+ *   lie in the job array or a pool: every job is read before the first is written.
  * max_n: the largest n any job may have (1..2^31).  A job with n outside
  *   [1, max_n] or a window leaving a pool reads nothing and gets NaN.
  * tuning: host struct, read during the call (item sizes: multiples of 1024).

@@ -151,10 +151,13 @@ __device__ inline uint32_t block_sum_u32(uint32_t v, uint32_t* s4) {
   return (s4[0] + s4[1]) + (s4[2] + s4[3]);
 }
 
-// Partial sums of whole blocks are combined in float64: they are few, and their
+// Partial sums of whole blocks are combined in float64 where a job is dispatched on its
+// own (vec_final) and in one-kernel images: they are few, and their
 // float32 sum rounded as much as all of the blocks' did.  Root mean square error
 // against float64, relative: 3000 uneven vector jobs 1.3e-7 -> 9.9e-8, images of
-// 333 x 250 4.1e-8 -> 2.5e-8.  The steps are wave_total_f32's.
+// 333 x 250 4.1e-8 -> 2.5e-8.  The register-window images' finaliser (sobel_final) and
+// batches' and no-allocation calls' jobs (vec_job_total) add in float32, as they always
+// have; a batch and a call without allocation give the same bits.  The steps are wave_total_f32's.
 template <int CTRL, int ROWS = 0xf>
 __device__ inline double dpp_f64(double v) {
   const uint64_t u = (uint64_t)__double_as_longlong(v);
@@ -1222,7 +1225,8 @@ template __global__ void k_hotspot_win_f32<false>(HotspotArgs a);
 // launch take about the time of three of one step; on a large one a launch is
 // bound by the vector ALU (6 instructions a cell and step, 1.8 cells computed
 // for each stored at S = 8) where one step was bound by memory.  64 jobs of
-// 256^2 and 16 steps: 1630 -> 1200 us; one of 1500 x 2000 and 32: 947 -> 794.
+// 256^2 and 16 steps, a step / 16 to a launch: 1558 / 799 us; one of 2000 x 1500 and
+// 32, a step / 8 to a launch: 942 / 765.
 // The inner rows of a group are stepped between the LDS reads and their use:
 // 8 steps of 4096^2 71.8 -> 62.3 us, 16 of 256^2 10.4 -> 10.1 us.  With 6
 // instructions instead of 9 a cell, and the lane shifts within the additions

@@ -183,7 +183,8 @@ inline uint64_t sobel_partials(int h, int w) {
 // that are not a multiple of 4, whose pair of kernels stages tiles in LDS as
 // well, twice.  Four jobs in the synchronous model, us, as a pair / in one:
 // 128^2 93 / 80, 333 x 250 117 / 103, 512^2 161 / 155, 1023 x 700 306 / 293,
-// 1501 x 1400 722 / 703; on the register windows 1024^2 390 / 384 and 2048^2
+// 1501 x 1400 722 / 703; one of 4097^2 1264 / 1260, of 16383 x 16381, near the largest
+// allowed, 19834 / 19830; on the register windows 1024^2 390 / 384 and 2048^2
 // 1300 / 1309, so the line is drawn where the pair's second pass over memory
 // stops costing more than the one kernel's passes through LDS.
 constexpr int kGsBlock = 512;
@@ -217,10 +218,13 @@ inline Grid3 hotspot_grid(int h, int w) {
 // steps rounded up to 4 cells.  On a small grid a launch is latency and more
 // steps cost little; on a large one the halo's cells are computed for nothing
 // (3 of 4 at 16 steps).  One job, us from submit to drained, at 1 (the one-step
-// kernels) / 4 / 8 / 16 steps a launch: 256^2, K = 16: 101 / 96 / 91 / 79;
-// 512^2, K = 16: 153 / 135 / 128 / 125; 1024^2, K = 16: 344 / 317 / 311 / 320;
-// 1500 x 2000, K = 32: 947 / 803 / 794 / 841; 4096^2, K = 16: 4217 / 3837 /
-// 3825 / 3971.
+// kernels) / 4 / 8 / 16 steps a launch: 256^2, K = 16: 98 / 74 / 64 / 62;
+// 512^2, K = 16: 145 / 132 / 122 / 120; 700^2, K = 16: 216 / 177 / 169 / 169; 1024^2,
+// K = 16: 339 / 324 / 307 / 311; 2000 x 1500, K = 32: 942 / 785 / 765 / 784; 4096^2,
+// K = 16: 4214 / 3824 / 3766 / 3838; 64 jobs of 256^2 1558 / 961 / 850 / 799.
+// The one-step kernels serve jobs of one step: cold, us, one of them / the steps kernel
+// with one step: 64^2 2.9 / 4.6, 333 x 250 7.7 / 9.2, 1024^2 3.8 / 6.8, 2048^2 8.8 /
+// 13.7, 8192^2 135 / 160 (of eleven sizes only odd 4099^2 the other way, 52 / 45).
 constexpr int kHotTile = 64;
 // Up to this many cells a job's last launch writes the grid to host memory itself.
 // Jobs, us, with an output copy / so: 64 of 32^2 402-465 / 354-396, one 47-51 / 40,
