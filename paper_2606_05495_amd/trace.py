@@ -414,11 +414,12 @@ def pmc_values(dirpath: str, counter: str):
     return [(d, n, v) for d, (n, v) in sorted(acc.items())]
 
 
-def loop_average(values, name_part: str, last: int):
+def loop_average(values, name_part, last: int):
     """Mean counter value over the last `last` dispatches of the kernel whose
-    name contains name_part (a cold loop's timed launches, which come after
+    name contains name_part, or one of several such parts (a cold loop's timed launches, which come after
     the batch's dispatches, the untimed passes and the loop's head start)."""
-    v = [x for _, n, x in values if name_part in n][-last:]
+    parts = (name_part,) if isinstance(name_part, str) else name_part
+    v = [x for _, n, x in values if any(p in n for p in parts)][-last:]
     return (sum(v) / len(v), len(v)) if v else (None, 0)
 
 
@@ -427,7 +428,7 @@ def traffic_record(fetch_dir: str, write_dir: str, kernels: dict, last: int, cal
     """HBM bytes per launch of each kernel from FETCH_SIZE and WRITE_SIZE runs
     (KiB per dispatch), each scaled by the factor that makes the counter read
     calib_bytes for a plain copy of calib_bytes (the last copy kernel of the
-    run).  kernels: {label: name_part}."""
+    run).  kernels: {label: name_part or several}."""
     fv, wv = pmc_values(fetch_dir, "FETCH_SIZE"), pmc_values(write_dir, "WRITE_SIZE")
     fc = [x for _, n, x in fv if calib_name in n]
     wc = [x for _, n, x in wv if calib_name in n]
@@ -494,13 +495,14 @@ def traffic_file(out_path: str, runs: dict, calib_bytes: int = 64 << 20) -> dict
                      "(__amd_rocclr_copyBuffer); mean over the timed cold-loop dispatches of stage_probe "
                      "--cold-only (each kernel's last `reps` dispatches)",
            "workloads": {}}
+    # the finaliser's name says whether it writes the output to host memory itself
+    kernels = {"gauss5_f32": "k_gauss5", "sobel_thresh_f32": "k_sobel_thresh",
+               "sobel_final": ("k_sobel_final", "k_copy_out_sobel")}
     for name, (fdir, wdir, probe) in runs.items():
         line = [l for l in open(probe) if l.startswith("{")][-1]
         probe_rec = json.loads(line)
         slots = probe_rec["slots"]
-        r = traffic_record(fdir, wdir, {"gauss5_f32": "k_gauss5", "sobel_thresh_f32": "k_sobel_thresh",
-                                        "sobel_final": "k_sobel_final"}, last=int(probe_rec.get("reps", 100)),
-                           calib_bytes=calib_bytes)
+        r = traffic_record(fdir, wdir, kernels, last=int(probe_rec.get("reps", 100)), calib_bytes=calib_bytes)
         r["slots"] = slots
         rec["workloads"][name] = r
     with open(out_path, "w") as fh:

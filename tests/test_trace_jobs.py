@@ -78,3 +78,17 @@ def test_batches_end_with_their_last_stage(tmp_path, last):
                  (1, t + 27, t + 34, last)]
     _csv(tmp_path, rows)
     assert trace.analyze_dir(str(tmp_path), batch=2)["mean_inter_batch_us"] == pytest.approx(7 / 1e3)
+
+
+@pytest.mark.parametrize("final", ["k_sobel_final", "k_copy_out_sobel"])
+def test_traffic_of_the_finaliser_under_both_names(tmp_path, final):
+    for d, counter, kib in (("f", "FETCH_SIZE", 32768.0), ("w", "WRITE_SIZE", 65536.0)):
+        (tmp_path / d).mkdir()
+        with open(tmp_path / d / "pmc_counter_collection.csv", "w") as fh:
+            fh.write("Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value\n")
+            fh.write('1,"setrt::%s(Args)",%s,8.0\n' % (final, counter))
+            fh.write('2,"__amd_rocclr_copyBuffer",%s,%f\n' % (counter, kib))
+    (tmp_path / "p.json").write_text('{"slots": 8, "reps": 1}\n')
+    r = trace.traffic_file(str(tmp_path / "out.json"), {"x": (str(tmp_path / "f"), str(tmp_path / "w"), str(tmp_path / "p.json"))})
+    k = r["workloads"]["x"]["kernels"]["sobel_final"]
+    assert k["fetch"] == 2 * 8192 and k["write"] == 8192
