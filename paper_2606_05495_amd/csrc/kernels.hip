@@ -1598,7 +1598,7 @@ __device__ __forceinline__ void vec_tiles(const VecBatchDesc* D, uint32_t count,
     auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
     auto scalar64 = [&](uint64_t v) { return (uint64_t)scalar((uint32_t)(v >> 32)) << 32 | scalar((uint32_t)v); };
     const uint32_t te = scalar(d.tile_elems), n = scalar(d.n);
-    const uint32_t ue = planned ? scalar(d.unit_elems) : vec_hand_unit(te, BLOCK);
+    const uint32_t ue = planned ? scalar(d.unit_elems) : vec_unit_elems(te, BLOCK);
     const uint64_t beg = (uint64_t)(t - scalar(d.tile_start)) * te;
     const uint64_t len = beg + te < n ? te : beg < n ? n - beg : 0;
     const float av = __int_as_float((int)scalar((uint32_t)__float_as_int(d.a)));

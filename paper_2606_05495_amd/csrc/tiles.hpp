@@ -55,15 +55,13 @@ inline uint32_t vec_default_tile(int b) {
 // four rounds of vec_range_sum's loads: after a unit of one round a block's
 // waves are in step, loading and then computing together (1024 threads, jobs of
 // 2^20 and more: 6.7 TB/s with 16384-element units against 6.9 with whole items
-// of 65536).  Items are multiples of 1024, so units are multiples of 256.
+// of 65536).  Items are multiples of 1024, so units are multiples of 256; one that is
+// not (a table submitted by hand, a serving call's tuning) stays whole, since it has
+// no four equal parts.
 SETRT_HD inline uint32_t vec_unit_elems(uint32_t item_elems, int block) {
+  if (item_elems % 1024u) return item_elems;
   const uint32_t least = 64u * (uint32_t)block;
   return item_elems / 4u >= least ? item_elems / 4u : item_elems / 2u >= least ? item_elems / 2u : item_elems;
-}
-// The same for a table submitted by hand, whose items may be of any size: the
-// library's split where it is even, else the whole item.
-SETRT_HD inline uint32_t vec_hand_unit(uint32_t item_elems, int block) {
-  return item_elems % 1024u ? item_elems : vec_unit_elems(item_elems, block);
 }
 // Units a block claims at a time.  A claim is an atomic on one word of the whole
 // device, which takes them at about 70 a microsecond: units of 1024 elements,

@@ -1,6 +1,7 @@
 """Vector batches whose descriptor table is submitted by hand, with set_submit:
 only the words that describe the jobs and their work items count, whatever the
 table's padding holds."""
+import ctypes
 import sys
 
 import numpy as np
@@ -84,3 +85,38 @@ def test_tables_by_hand(torch_gpu, pools, room, block):
                     for j, s in zip(jobs, got):
                         S, E = oracle.saxpy_tanh_sum(x[j["x_off"]:j["x_off"] + j["n"]], y[j["y_off"]:j["y_off"] + j["n"]], j["a"])
                         assert abs(float(s) - S) <= oracle.vec_tolerance(S, E), (item, int(j["n"]), s, S)
+
+
+@pytest.mark.parametrize("room", [64, 4096])  # tiles_max: a block takes whole items, or their units
+@pytest.mark.parametrize("item", [1000, 65539, 131079, 200003])
+def test_serving_with_items_of_any_size(torch_gpu, pools, item, room):
+    """set_serve takes its tuning's item sizes as they are: one that has no four equal
+    parts is summed whole, with the bits of the same request in a batch by hand."""
+    print("serving, items of", item, room)
+    sys.stdout.flush()
+    x, y, xd, yd = pools
+    rng = np.random.default_rng(item)
+    n = np.array([1, 999, 1001, 60000])[:, None].repeat(4, 1).ravel() if item == 1000 else rng.integers(1, 800000, 16)
+    req = np.zeros(len(n), A.REQUEST_DTYPE)
+    req["n"], req["a"], req["worker_hint"] = n, rng.uniform(0.5, 2, len(n)), -1
+    req["x_off"], req["y_off"] = rng.integers(0, POOL - n), rng.integers(0, POOL - n)
+    tune = A.set_vec_tuning()
+    for b in range(64):
+        tune.tile_elems[b] = item
+    cfg = A.set_serve_config()
+    cfg.tuning = ctypes.pointer(tune)
+    got = np.zeros(len(n), np.float32)
+    with Context(mode="set", workers=2, slots=2, callback="host_flag") as ctx:
+        tid = ctx.define("saxpy_batch", max_n=POOL, x_pool=xd, y_pool=yd, batch_max=8, tiles_max=room, copy="async_in")
+        req["template_id"] = tid
+        _, st = A.set_serve(ctx.h, req, cfg, got)
+        assert st.completed == len(n) and st.failed == 0
+        tin, nin = pinned(64 + 48)
+        tout, nout = pinned(64 + 4)
+        for j, s in zip(req, got):
+            _table(nin, np.array([j]), item, 0, 0)
+            ctx.submit(tid, host_in=tin.data_ptr(), in_bytes=64 + 48, host_out=tout.data_ptr(), out_bytes=68, n=1)
+            ctx.drain()
+            assert nout[64:68].tobytes() == s.tobytes(), (item, int(j["n"]))
+            S, E = oracle.saxpy_tanh_sum(x[j["x_off"]:j["x_off"] + j["n"]], y[j["y_off"]:j["y_off"] + j["n"]], j["a"])
+            assert abs(float(s) - S) <= oracle.vec_tolerance(S, E), (item, int(j["n"]), s, S)
