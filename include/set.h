@@ -600,7 +600,9 @@ typedef struct set_serve_stats {
  * of the run (the arrival time is reqs[i].t_arrival_ns; 0 = not completed);
  * vec_results[i] receives S of vector request i (may be NULL if there are
  * none).  Blocks until every admitted request completed.  The per-job
- * requests' host buffers follow set_submit's rules. */
+ * requests' host buffers follow set_submit's rules.  SET_EINVAL, before
+ * anything is admitted, if a vector request alone needs more work items than
+ * its template's tiles_max. */
 int set_serve(set_ctx *c, const set_request *reqs, uint64_t count, const set_serve_config *cfg,
               uint64_t *done_ns, float *vec_results, set_serve_stats *stats);
 

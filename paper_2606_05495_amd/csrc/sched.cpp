@@ -1188,6 +1188,9 @@ class Context {
         if (q.args.n < 1 || q.args.n > t.max_n || q.args.x_off > t.pool_len || q.args.n > t.pool_len - q.args.x_off ||
             q.args.y_off > t.pool_len || q.args.n > t.pool_len - q.args.y_off)
           return fail(SET_EINVAL, "vector request outside the template's limits");
+        const int bk = 63 - __builtin_clzll(q.args.n);
+        const uint32_t te = (sc.tuning && sc.tuning->tile_elems[bk]) ? sc.tuning->tile_elems[bk] : vec_default_tile(bk);
+        if ((q.args.n + te - 1) / te > t.tiles_max) return fail(SET_EINVAL, "a request needs more work items than tiles_max");
         ++nvec;
       } else if (pipeline_validate_job(t, q.args, &why) != SET_OK) {
         return fail(SET_EINVAL, why);
